@@ -198,7 +198,9 @@ lbm_status lbm_sample(lbm_solver *h, int n, const int *x, const int *y, double *
 /* Launch shape of the step kernel: threads per block (64, 128, 256 or 512;
  * one lattice column per thread) and row segments per column strip
  * (1 <= n_segs <= ny). Results do not depend on it (bitwise); it only
- * changes speed. lbm_create picks a default; the autotuner overrides it. */
+ * changes speed. lbm_create picks a default; the autotuner overrides it.
+ * Setting it makes the fused step kernel run the plate where it can (see
+ * lbm_set_general_path). */
 lbm_status lbm_set_tiling(lbm_solver *h, int block, int n_segs);
 lbm_status lbm_get_tiling(const lbm_solver *h, int *block, int *n_segs);
 
@@ -222,14 +224,15 @@ lbm_status lbm_get_steps_per_launch(const lbm_solver *h, int *k);
  * chosen with it. Writes 0 for a shape the handle cannot launch. */
 lbm_status lbm_resident_blocks(const lbm_solver *h, int block, int steps_per_launch, int *blocks);
 
-/* Run every step as the general step (1: one launch of 2D tiles, each
- * holding its whole neighbourhood in LDS) or, when no x edge is a wall, as
- * the fused step kernel (0, the default). Both give the same results up to
- * rounding. The general step runs walls on the x edges, holes and the
- * extrapolation scheme; on small plates it is also the faster one (its
- * tiles' stages run in parallel where the fused kernel marches rows one
- * after another). Needs no workspace beyond what the plate's edges, mask
- * and scheme already need. */
+/* Run every step as the general step (1: 2D windows of the plate, each
+ * holding its whole neighbourhood in registers and LDS) or, when no x edge is
+ * a wall, as the fused step kernel (0). Both give the same results, bit for
+ * bit where the fused kernel can run. The general step runs walls on the x
+ * edges, holes and the extrapolation scheme; on small plates it is also the
+ * faster one (its stages run on the whole window in parallel where the fused
+ * kernel marches rows one after another), and until this call or a launch
+ * shape of the fused kernel is set the library picks it for them. Needs no
+ * workspace beyond what the plate's edges, mask and scheme already need. */
 lbm_status lbm_set_general_path(lbm_solver *h, int on);
 
 /* Holes in the plate (the plate with a hole of Sec. 7.2). solid: host array

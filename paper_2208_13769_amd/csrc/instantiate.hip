@@ -6,10 +6,12 @@
 // declare these instantiations.
 #include "general_kernels.hpp"
 #include "host_common.hpp"
+#include "window_kernel.hpp"
 
 namespace lbm {
 
 template struct Kernels<LBM_PREC>;
 template hipError_t general_step<LBM_PREC>(GenParams, char *, hipStream_t);
+template hipError_t window_step<LBM_PREC>(GenParams, int, int, char *, hipStream_t);
 
 }  // namespace lbm

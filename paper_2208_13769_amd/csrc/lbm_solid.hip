@@ -15,6 +15,7 @@
 
 #include "general_kernels.hpp"
 #include "host_common.hpp"
+#include "window_kernel.hpp"
 
 using namespace lbm;
 
@@ -113,6 +114,7 @@ struct lbm_solver {
     int sr = 0;   // stochastic rounding of 16-bit populations
     unsigned long long seed = 0;
     bool force_general = false;  // run the general step even without x walls
+    bool fused_set = false;      // the caller chose the fused kernel or its launch shape
     bool has_mask = false;       // holes (lbm_set_mask)
     std::vector<unsigned char> mask_host;  // host copy of the mask (1 material, 0 hole)
     bool tables_dirty = true;    // the general step's tile table and fused list need rebuilding
@@ -139,6 +141,28 @@ struct lbm_solver {
     {
         return force_general || has_mask || bc[LBM_EDGE_XMIN] != LBM_BC_PERIODIC || scheme == LBM_SCHEME_EXTRAP;
     }
+    // Whether windows (window_kernel.hpp) run the plate's steps in place of
+    // the fused kernel or of the general step's fused share: always where the
+    // caller asked for the general step or j is extrapolated; else, unless the
+    // caller chose the fused kernel or its shape, up to the plate size where
+    // the fused kernel's best launch shape caught up. us per step, windows
+    // against that: periodic FP64 700^2 31.9 / 31.8, FP32 1000^2 27.6 / 27.1,
+    // FP32_U64 1400^2 53 / 48, FP16 1400^2 65 / 61; y walls FP64 700^2 38 / 38,
+    // FP32 1000^2 33.9 / 34.1, FP32_U64 1000^2 41 / 38, FP16 1000^2 44.5 /
+    // 43.2; walls and holes FP64 1000^2 76 / 66, FP32 38 / 45, FP16 2000^2
+    // 178 / 149. Narrow plates go by their number of sites too.
+    bool windows() const
+    {
+        if (scheme == LBM_SCHEME_EXTRAP || (force_general && !split_edges())) return true;
+        if (fused_set && !split_edges()) return false;
+        static const double limit[3][4] = {{5e5, 1.0e6, 1.2e6, 1.2e6},   // periodic: FP64, FP32, FP32_U64, 16-bit
+                                           {5e5, 1.0e6, 0.7e6, 1.0e6},   // y walls
+                                           {7e5, 1.2e6, 1.2e6, 2.4e6}};  // x walls or holes
+        const int kind = split_edges() ? 2 : bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC ? 1 : 0;
+        return (double)nx * ny <= limit[kind][win_class(prec)];
+    }
+    // x walls or holes: the fused kernel can run a share of the plate at most
+    bool split_edges() const { return has_mask || bc[LBM_EDGE_XMIN] != LBM_BC_PERIODIC; }
     const unsigned char *mask_ptr() const
     {
         return has_mask ? reinterpret_cast<const unsigned char *>(ws + L.mask) : nullptr;
@@ -436,6 +460,7 @@ lbm_status lbm_set_tiling(lbm_solver *h, int block, int n_segs)
     if (h->spl == 2 && !two_step_fits(h, block))
         return fail(h, LBM_ERR_UNSUPPORTED, "two steps per launch with this block size exceed the LDS");
     h->shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, n_segs, h->spl);
+    h->fused_set = true;
     return LBM_OK;
 }
 
@@ -448,6 +473,7 @@ lbm_status lbm_set_steps_per_launch(lbm_solver *h, int k)
     if (k == 2 && max_steps_per_launch(h->prec, h->scheme) < 2)
         return fail(h, LBM_ERR_UNSUPPORTED, "16-bit population storage runs one step per launch");
     h->spl = k;
+    h->fused_set = true;
     const int block = k == 2 && !two_step_fits(h, h->shape.block) ? 256 : h->shape.block;
     h->shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, h->shape.n_segs, k);
     return LBM_OK;
@@ -518,6 +544,7 @@ lbm_status lbm_set_general_path(lbm_solver *h, int on)
     // (holes, x walls and the extrapolation scheme already hold the walled
     // workspace; the general step of any other plate needs no more)
     h->force_general = on != 0;
+    h->fused_set = !on;
     return LBM_OK;
 }
 
@@ -854,7 +881,8 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     sp.seed = h->seed;
     const int nblocks = h->shape.n_strips * h->shape.n_segs;
     const bool pc = h->scheme == LBM_SCHEME_PC;
-    if (h->general()) {
+    const bool windows = h->windows();
+    if (windows || h->general()) {
         GenParams gp{};
         gp.nx = h->nx;
         gp.ny = h->ny;
@@ -865,11 +893,11 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         gp.bx = sp.bx;
         gp.by = sp.by;
         const Units U = h->units();
+        const double sl = 1.0 / U.stress();
         for (int e = 0; e < 4; ++e) {
             gp.bc[e] = h->bc[e];
-            for (int a = 0; a < 2; ++a) {  // j* -> lattice momentum, T* -> lattice stress
-                gp.val[e][a] = h->bc[e] == LBM_BC_DIRICHLET_J ? h->bcval[e][a] / U.momentum()
-                                                              : h->bcval[e][a] / U.stress();
+            for (int a = 0; a < 2; ++a) {  // j* -> lattice momentum, T* -> lattice stress (rounded as fill_physics does)
+                gp.val[e][a] = h->bc[e] == LBM_BC_DIRICHLET_J ? h->bcval[e][a] / U.momentum() : h->bcval[e][a] * sl;
                 gp.uwb[e][a] = h->uwb[e][a];
             }
         }
@@ -880,6 +908,30 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         gp.pc = h->scheme == LBM_SCHEME_EXTRAP ? 2 : (pc ? 1 : 0);
         gp.flag = sp.flag;
         gp.mask = h->mask_ptr();
+        if (windows) {
+            const int reach = pc || gp.pc ? win_reach<1>() : win_reach<0>();
+            const bool gen = h->split_edges() || h->bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC;
+            auto choose = [&](int max_steps) {
+                return choose_window(win_class(h->prec), gen, h->nx, h->ny, reach, deviation_storage(h->prec),
+                                     max_steps);
+            };
+            WinChoice c = choose(nsteps >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
+            for (int64_t k = 0; k < nsteps; k += c.steps) {
+                if (k + c.steps > nsteps) c = choose(1);  // an odd last step
+                gp.f_in = h->fptr(h->cur);
+                gp.u_in = h->uptr(h->cur);
+                gp.j_in = h->jptr(h->cur);
+                gp.f_out = h->fptr(h->cur ^ 1);
+                gp.u_out = h->uptr(h->cur ^ 1);
+                gp.j_out = h->jptr(h->cur ^ 1);
+                gp.step = h->steps;
+                HIP_TRY(h, LBM_DISPATCH(h->prec, window_step<PR>(gp, c.shape, c.steps, h->ws + h->L.scratch,
+                                                                 h->stream)));
+                h->cur ^= 1;
+                h->steps += c.steps;
+            }
+            return LBM_OK;
+        }
         if (h->tables_dirty && h->ws_bytes >= h->L.total_walled) HIP_TRY(h, build_general_tables(h));
         gp.tiles = h->tiles_ptr();
         // without holes and without a fused share the table marks every

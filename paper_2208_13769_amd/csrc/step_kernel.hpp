@@ -196,19 +196,18 @@ __device__ __forceinline__ void collide(const TC f[9], TC jx, TC jy, TC Sx, TC S
 // A* = Pbar* - r_bd/3 I, with Pbar*_12 = Pbar*_21 = -s T*_1 + K_12,
 // Pbar*_22 = -s T*_2 + K_22, Pbar*_11 = Pi_11 (outward normal (0, s)); k12
 // and k22 are K at the wall (the caller passes the mean of the node row and
-// the ghost row).
+// the ghost row). fco: the outgoing links 2, 5, 6 (top) or 4, 7, 8.
 template <class TC>
-__device__ __forceinline__ void wall_populations(bool top, int kind, const TC fc[9], const double val[2],
+__device__ __forceinline__ void wall_populations(bool top, int kind, const TC fco[3], const double val[2],
                                                  TC r, TC pxx, TC k12, TC k22, TC out[3])
 {
-    const int i0 = top ? 2 : 4, i1 = top ? 5 : 7, i2 = top ? 6 : 8;
     if (kind == BC_DIRICHLET) {
         const TC jx = TC(val[0]), jy = TC(val[1]);
         const TC sy = top ? TC(1) : TC(-1);  // e_y of the outgoing links
-        out[0] = fc[i0] - TC(6.0 / 9.0) * (sy * jy);
-        // i1: e = (sy, sy) for top (1,1) / bottom (-1,-1); i2: (-1, 1) top / (1, -1) bottom
-        out[1] = fc[i1] - TC(6.0 / 36.0) * (sy * jx + sy * jy);
-        out[2] = fc[i2] - TC(6.0 / 36.0) * (-sy * jx + sy * jy);
+        out[0] = fco[0] - TC(6.0 / 9.0) * (sy * jy);
+        // fco[1]: e = (1, 1) top / (-1, -1) bottom; fco[2]: (-1, 1) top / (1, -1) bottom
+        out[1] = fco[1] - TC(6.0 / 36.0) * (sy * jx + sy * jy);
+        out[2] = fco[2] - TC(6.0 / 36.0) * (-sy * jx + sy * jy);
     } else {
         const TC s = top ? TC(1) : TC(-1);
         const TC p12 = -s * TC(val[0]) + k12;
@@ -219,9 +218,9 @@ __device__ __forceinline__ void wall_populations(bool top, int kind, const TC fc
         const TC q2 = ayy - trA * third;
         const TC q5 = TC(2) * (trA * third + p12);
         const TC q6 = TC(2) * (trA * third - p12);
-        out[0] = -fc[i0] + TC(2.0 / 9.0) * (r + TC(4.5) * q2);
-        out[1] = -fc[i1] + TC(2.0 / 36.0) * (r + TC(4.5) * q5);
-        out[2] = -fc[i2] + TC(2.0 / 36.0) * (r + TC(4.5) * q6);
+        out[0] = -fco[0] + TC(2.0 / 9.0) * (r + TC(4.5) * q2);
+        out[1] = -fco[1] + TC(2.0 / 36.0) * (r + TC(4.5) * q5);
+        out[2] = -fco[2] + TC(2.0 / 36.0) * (r + TC(4.5) * q6);
     }
 }
 
@@ -662,16 +661,18 @@ struct Pipe {
             collide(fl, jx, jy, Sx, Sy, omega, fc, r, pxx);
             // K at a wall: the mean of the node row and the ghost row beyond it
             if (WALLED && rC == 0) {
+                const TC fco[3] = {fc[4], fc[7], fc[8]};
                 TC w[3];
-                wall_populations(false, bc_lo, fc, val_lo, r, pxx, TC(0.5) * (kA2.template at<PH, 1>(0) + k12d),
+                wall_populations(false, bc_lo, fco, val_lo, r, pxx, TC(0.5) * (kA2.template at<PH, 1>(0) + k12d),
                                  TC(0.5) * (kA2.template at<PH, 1>(1) + k22d), w);
                 L.wall[0][0][t] = w[0];
                 L.wall[0][1][t] = w[1];
                 L.wall[0][2][t] = w[2];
             }
             if (WALLED && rC == ny - 1) {
+                const TC fco[3] = {fc[2], fc[5], fc[6]};
                 TC w[3];
-                wall_populations(true, bc_hi, fc, val_hi, r, pxx,
+                wall_populations(true, bc_hi, fco, val_hi, r, pxx,
                                  TC(0.5) * (kA2.template at<PH, 1>(0) + kA2.template at<PH, 0>(0)),
                                  TC(0.5) * (kA2.template at<PH, 1>(1) + kA2.template at<PH, 0>(1)), w);
                 L.wall[WALLED ? 1 : 0][0][t] = w[0];
