@@ -12,6 +12,6 @@ namespace lbm {
 
 template struct Kernels<LBM_PREC>;
 template hipError_t general_step<LBM_PREC>(GenParams, char *, hipStream_t);
-template hipError_t window_step<LBM_PREC>(GenParams, int, int, char *, hipStream_t);
+template hipError_t window_step<LBM_PREC>(GenParams, int, int, int, char *, hipStream_t);
 
 }  // namespace lbm

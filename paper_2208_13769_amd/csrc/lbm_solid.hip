@@ -161,6 +161,8 @@ struct lbm_solver {
         const int kind = split_edges() ? 2 : bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC ? 1 : 0;
         return (double)nx * ny <= limit[kind][win_class(prec)];
     }
+    // any wall or hole
+    bool walls() const { return split_edges() || bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC; }
     // x walls or holes: the fused kernel can run a share of the plate at most
     bool split_edges() const { return has_mask || bc[LBM_EDGE_XMIN] != LBM_BC_PERIODIC; }
     const unsigned char *mask_ptr() const
@@ -893,11 +895,15 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         gp.bx = sp.bx;
         gp.by = sp.by;
         const Units U = h->units();
-        const double sl = 1.0 / U.stress();
+        // windows of a plate that the fused kernel can run keep its arithmetic
+        const int edges = h->general() ? (h->walls() ? WIN_GENERAL : WIN_PERIODIC)
+                                       : (h->walls() ? WIN_YWALLS : WIN_PERIODIC);
         for (int e = 0; e < 4; ++e) {
             gp.bc[e] = h->bc[e];
-            for (int a = 0; a < 2; ++a) {  // j* -> lattice momentum, T* -> lattice stress (rounded as fill_physics does)
-                gp.val[e][a] = h->bc[e] == LBM_BC_DIRICHLET_J ? h->bcval[e][a] / U.momentum() : h->bcval[e][a] * sl;
+            for (int a = 0; a < 2; ++a) {  // j* -> lattice momentum, T* -> lattice stress (each path's own rounding)
+                gp.val[e][a] = h->bc[e] == LBM_BC_DIRICHLET_J ? h->bcval[e][a] / U.momentum()
+                               : edges == WIN_GENERAL         ? h->bcval[e][a] / U.stress()
+                                                              : h->bcval[e][a] * (1.0 / U.stress());
                 gp.uwb[e][a] = h->uwb[e][a];
             }
         }
@@ -910,7 +916,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         gp.mask = h->mask_ptr();
         if (windows) {
             const int reach = pc || gp.pc ? win_reach<1>() : win_reach<0>();
-            const bool gen = h->split_edges() || h->bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC;
+            const bool gen = edges != WIN_PERIODIC;
             auto choose = [&](int max_steps) {
                 return choose_window(win_class(h->prec), gen, h->nx, h->ny, reach, deviation_storage(h->prec),
                                      max_steps);
@@ -925,8 +931,8 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
                 gp.u_out = h->uptr(h->cur ^ 1);
                 gp.j_out = h->jptr(h->cur ^ 1);
                 gp.step = h->steps;
-                HIP_TRY(h, LBM_DISPATCH(h->prec, window_step<PR>(gp, c.shape, c.steps, h->ws + h->L.scratch,
-                                                                 h->stream)));
+                HIP_TRY(h, LBM_DISPATCH(h->prec, window_step<PR>(gp, edges, c.shape, c.steps,
+                                                                 h->ws + h->L.scratch, h->stream)));
                 h->cur ^= 1;
                 h->steps += c.steps;
             }

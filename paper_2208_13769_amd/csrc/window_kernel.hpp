@@ -19,7 +19,8 @@
 // that node reads it), so the streaming stage itself has no wall code.
 //
 // The arithmetic of a site is the fused step kernel's, expression by
-// expression (y walls included), so both give the same bits.
+// expression (y walls included), so both give the same bits; plates with x
+// walls or holes keep one arithmetic too, whatever shape and split runs them.
 //
 // Bound: on small plates the latency of a launch, of the load and of five
 // stages (about 400 vector instructions a site on periodic plates, walls three
@@ -64,7 +65,12 @@ constexpr int win_reach()
     return MODE ? 5 : 3;
 }
 
-template <class PR, int MODE, int WW, int WH, int K, bool GEN>
+// Edges a window is built for: periodic plates; y walls between periodic x
+// edges, in the fused kernel's arithmetic; walls on any edge, holes and the
+// extrapolation variant beside walls, in the general rules' arithmetic.
+enum : int { WIN_PERIODIC = 0, WIN_YWALLS = 1, WIN_GENERAL = 2 };
+
+template <class PR, int MODE, int WW, int WH, int K, int GEN>
 struct Window {
     using TF = typename PR::TF;
     using TU = typename PR::TU;
@@ -79,12 +85,12 @@ struct Window {
         TU u[2][N];
         TC k[4][N];
         TC f[8][N];  // directions 1..8
-        unsigned char hole[GEN ? N : 1];
+        unsigned char hole[GEN == WIN_GENERAL ? N : 1];
     };
 
     // bits of a site's flags
     enum : unsigned { NODE = 1u, GHOST = 2u, XL = 4u, XH = 8u, YL = 16u, YH = 32u, EDGE = XL | XH | YL | YH, HOLE = 64u,
-                      BOTTOM = 128u /* ghost row below the bottom wall, x periodic */, NEAR = 256u /* << direction: hole there */ };
+                      BOTTOM = 128u /* ghost row below the bottom wall */, NEAR = 256u /* << direction: hole there */ };
 
     const GenParams &p;
     Lds &L;
@@ -111,7 +117,8 @@ struct Window {
         L.u[1][i] = u1;
         if (!GEN || !(fl & EDGE)) return;
         fl = opaque(fl);
-        const bool lo_y = fl & YL, lo_x = fl & XL, on_y = fl & (YL | YH), on_x = fl & (XL | XH);
+        const bool lo_y = fl & YL, on_y = fl & (YL | YH);
+        const bool lo_x = GEN == WIN_GENERAL && (fl & XL), on_x = GEN == WIN_GENERAL && (fl & (XL | XH));
         const int dx = lo_x ? -1 : 1, dy = lo_y ? -1 : 1;
         const int bcx = lo_x ? p.bc[EDGE_XMIN] : p.bc[EDGE_XMAX], bcy = lo_y ? p.bc[EDGE_YMIN] : p.bc[EDGE_YMAX];
         const bool x1 = (unsigned)(lx + dx) < (unsigned)WW, x2 = (unsigned)(lx + 2 * dx) < (unsigned)WW;
@@ -139,13 +146,13 @@ struct Window {
     __device__ __forceinline__ static bool near(unsigned fl, int dir) { return (fl >> (8 + dir)) & 1u; }
 
     // Central-difference gradient of the displacement in LDS at site i (a
-    // hole neighbour takes the node's own value). Between periodic x edges the
+    // hole neighbour takes the node's own value). With y walls alone the
     // ghost row below the bottom wall takes the fused kernel's form: the row's x-derivatives from
     // row 0, negated beyond a momentum wall, whose ghosts 2 uw - u0 and
     // 4 uw - 3 u0 give the y-difference 2 (u0 - uw).
     __device__ __forceinline__ void grad(int i, unsigned fl, const double uw[4][2], TC H[4]) const
     {
-        if (GEN && (fl & BOTTOM)) {
+        if (GEN == WIN_YWALLS && (fl & BOTTOM)) {
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 const TU *r = L.u[a] + i + WW;
@@ -164,7 +171,7 @@ struct Window {
         for (int a = 0; a < 2; ++a) {
             const TU *r = L.u[a] + i;
             TU xp = r[1], xm = r[-1], yp = r[WW], ym = r[-WW];
-            if (GEN && (fl >> 8)) {
+            if (GEN == WIN_GENERAL && (fl >> 8)) {
                 const TU c = r[0];
                 if (near(fl, 1)) xp = c;
                 if (near(fl, 3)) xm = c;
@@ -189,7 +196,7 @@ struct Window {
     {
         TC xp0 = L.k[0][i + 1], xm0 = L.k[0][i - 1], xp2 = L.k[2][i + 1], xm2 = L.k[2][i - 1];
         TC yp1 = L.k[1][i + WW], ym1 = L.k[1][i - WW], yp3 = L.k[3][i + WW], ym3 = L.k[3][i - WW];
-        if (GEN && (fl >> 8)) {
+        if (GEN == WIN_GENERAL && (fl >> 8)) {
             TC kh[4];
             if (near(fl, 1) || near(fl, 3)) {
                 k_hole(H, 0, kh);
@@ -221,99 +228,87 @@ struct Window {
         return (bx ? 1 : 0) | (by ? 2 : 0);
     }
 
-    // Values the wall on the x side S (-1: left, 1: right) of node i returns,
-    // as wall_populations for y walls: Pbar*_11 = -s T*_1 + K_11, Pbar*_12 =
-    // -s T*_2 + K_21, Pbar*_22 = Pi_22. w: link (S, 0), then (S, 1), (S, -1).
-    template <int S>
-    __device__ __forceinline__ void side_x(int i, int kind, const double val[2], TC r, TC pyy, TC k11, TC k21, TC w[3])
+    // One wall of WIN_GENERAL on side S (-1: low, 1: high) of axis A of node i:
+    // the values it returns for the axis link and for the two diagonals that
+    // cross this wall alone, into the slots the pull reads. m: r, Pxx, Pyy,
+    // Pxy of the node's populations, whose values after the collision are in
+    // the LDS. eq. (25), (26) with r_bd and the tangential moments at the
+    // node; K at the wall is the mean of the node's and the one beyond it (a
+    // ghost node, or at a hole, T* = 0, the hole K the node sees).
+    template <int A, int S>
+    __device__ __forceinline__ void side(int i, unsigned fl, const TC H[4], const TC m[4])
     {
-        constexpr int o0 = S > 0 ? 1 : 3, o1 = S > 0 ? 5 : 6, o2 = S > 0 ? 8 : 7;
-        const TC s = TC(S), f0 = L.f[o0 - 1][i], f1 = L.f[o1 - 1][i], f2 = L.f[o2 - 1][i];
-        if (kind == BC_DIRICHLET) {
-            const TC jx = TC(val[0]), jy = TC(val[1]);
-            w[0] = f0 - TC(6.0 / 9.0) * (s * jx);
-            w[1] = f1 - TC(6.0 / 36.0) * (s * jx + jy);
-            w[2] = f2 - TC(6.0 / 36.0) * (s * jx - jy);
+        constexpr int o0 = A ? (S > 0 ? 2 : 4) : (S > 0 ? 1 : 3);
+        const bool hole = near(fl, o0);
+        if (!hole && !(fl & (A ? (S > 0 ? YH : YL) : (S > 0 ? XH : XL)))) return;
+        constexpr int e = A ? (S > 0 ? EDGE_YMAX : EDGE_YMIN) : (S > 0 ? EDGE_XMAX : EDGE_XMIN);
+        constexpr int o1 = A ? (S > 0 ? 5 : 8) : (S > 0 ? 5 : 6);  // diagonals: e_t = 1, then -1 along the wall
+        constexpr int o2 = A ? (S > 0 ? 6 : 7) : (S > 0 ? 8 : 7);
+        const TC f0 = L.f[o0 - 1][i], f1 = L.f[o1 - 1][i], f2 = L.f[o2 - 1][i];
+        const TC s = TC(S), w1 = TC(1.0 / 9.0), w5 = TC(1.0 / 36.0);
+        const double t0 = hole ? 0.0 : p.val[e][0], t1 = hole ? 0.0 : p.val[e][1];
+        TC v0, v1, v2;
+        if (!hole && p.bc[e] == BC_DIRICHLET) {
+            const TC jn = TC(A ? t1 : t0), jt = TC(A ? t0 : t1);
+            v0 = f0 - TC(6) * w1 * (s * jn);
+            v1 = f1 - TC(6) * w5 * (s * jn + jt);
+            v2 = f2 - TC(6) * w5 * (s * jn - jt);
         } else {
-            const TC p11 = -s * TC(val[0]) + k11;
-            const TC p12 = -s * TC(val[1]) + k21;
-            const TC third = TC(1) / TC(3);
-            const TC axx = p11 - r * third, ayy = pyy - r * third;
-            const TC trA = axx + ayy;
-            const TC q1 = axx - trA * third;
-            const TC qp = TC(2) * (trA * third + s * p12);
-            const TC qm = TC(2) * (trA * third - s * p12);
-            w[0] = -f0 + TC(2.0 / 9.0) * (r + TC(4.5) * q1);
-            w[1] = -f1 + TC(2.0 / 36.0) * (r + TC(4.5) * qp);
-            w[2] = -f2 + TC(2.0 / 36.0) * (r + TC(4.5) * qm);
+            const int g = A ? i + S * WW : i + S;
+            TC ka = L.k[A][g], kb = L.k[2 + A][g];
+            if (hole) {
+                TC kh[4];
+                k_hole(H, A, kh);
+                ka = kh[A];
+                kb = kh[2 + A];
+            }
+            // the wall's column of Pbar*
+            const TC q0 = -s * TC(t0) + TC(0.5) * (L.k[A][i] + ka), q1 = -s * TC(t1) + TC(0.5) * (L.k[2 + A][i] + kb);
+            const TC Pxx = A ? m[1] : q0, Pyy = A ? q1 : m[2], Pxy = A ? q0 : q1;
+            const TC r = m[0], third = TC(1) / TC(3);
+            const TC axx = Pxx - r * third, ayy = Pyy - r * third;
+            const TC tr = axx + ayy, an = A ? ayy : axx;
+            const TC d1 = (axx + TC(2) * (s * Pxy)) + ayy, d2 = (axx - TC(2) * (s * Pxy)) + ayy;
+            v0 = -f0 + TC(2) * w1 * (r + TC(4.5) * (an - tr * third));
+            v1 = -f1 + TC(2) * w5 * (r + TC(4.5) * (d1 - tr * third));
+            v2 = -f2 + TC(2) * w5 * (r + TC(4.5) * (d2 - tr * third));
         }
+        constexpr int only = A ? 2 : 1;
+        L.f[kGopp[o0] - 1][i + kGy[o0] * WW + kGx[o0]] = v0;
+        if (crossed(fl, o1, kGx[o1], kGy[o1]) == only) L.f[kGopp[o1] - 1][i + kGy[o1] * WW + kGx[o1]] = v1;
+        if (crossed(fl, o2, kGx[o2], kGy[o2]) == only) L.f[kGopp[o2] - 1][i + kGy[o2] * WW + kGx[o2]] = v2;
     }
 
-    template <int S>
-    __device__ __forceinline__ void wall_x(int i, unsigned fl, const TC H[4], TC r, TC pyy)
-    {
-        constexpr int o0 = S > 0 ? 1 : 3, o1 = S > 0 ? 5 : 6, o2 = S > 0 ? 8 : 7;
-        const bool hole = near(fl, o0);
-        if (!hole && !(fl & (S > 0 ? XH : XL))) return;
-        constexpr int e = S > 0 ? EDGE_XMAX : EDGE_XMIN;
-        TC k0 = L.k[0][i + S], k2 = L.k[2][i + S];
-        if (hole) {
-            TC kh[4];
-            k_hole(H, 0, kh);
-            k0 = kh[0];
-            k2 = kh[2];
-        }
-        const double val[2] = {hole ? 0.0 : p.val[e][0], hole ? 0.0 : p.val[e][1]};
-        TC w[3];
-        side_x<S>(i, hole ? (int)BC_NEUMANN : p.bc[e], val, r, pyy, TC(0.5) * (L.k[0][i] + k0),
-                  TC(0.5) * (L.k[2][i] + k2), w);
-        L.f[kGopp[o0] - 1][i + S] = w[0];
-        if (crossed(fl, o1, S, 1) == 1) L.f[kGopp[o1] - 1][i + S + WW] = w[1];
-        if (crossed(fl, o2, S, -1) == 1) L.f[kGopp[o2] - 1][i + S - WW] = w[2];
-    }
-
-    template <int S>
-    __device__ __forceinline__ void wall_y(int i, unsigned fl, const TC H[4], TC r, TC pxx)
-    {
-        // links of wall_populations: (0, S), (S, S), (-S, S)
-        constexpr int o0 = S > 0 ? 2 : 4, o1 = S > 0 ? 5 : 7, o2 = S > 0 ? 6 : 8;
-        const bool hole = near(fl, o0);
-        if (!hole && !(fl & (S > 0 ? YH : YL))) return;
-        constexpr int e = S > 0 ? EDGE_YMAX : EDGE_YMIN;
-        TC k1 = L.k[1][i + S * WW], k3 = L.k[3][i + S * WW];
-        if (hole) {
-            TC kh[4];
-            k_hole(H, 1, kh);
-            k1 = kh[1];
-            k3 = kh[3];
-        }
-        const double val[2] = {hole ? 0.0 : p.val[e][0], hole ? 0.0 : p.val[e][1]};
-        const TC fco[3] = {L.f[o0 - 1][i], L.f[o1 - 1][i], L.f[o2 - 1][i]};
-        TC w[3];
-        wall_populations(S > 0, hole ? (int)BC_NEUMANN : p.bc[e], fco, val, r, pxx, TC(0.5) * (L.k[1][i] + k1),
-                         TC(0.5) * (L.k[3][i] + k3), w);
-        L.f[kGopp[o0] - 1][i + S * WW] = w[0];
-        if (crossed(fl, o1, S, S) == 2) L.f[kGopp[o1] - 1][i + S * WW + S] = w[1];
-        if (crossed(fl, o2, -S, S) == 2) L.f[kGopp[o2] - 1][i + S * WW - S] = w[2];
-    }
-
-    // Values the walls return to node i, into the slots its pull reads. m: r,
-    // Pxx, Pyy, Pxy of its populations; its populations after the collision
-    // are in the LDS. One side at a time, three links each (a wall, or a hole
-    // with T* = 0 and the hole K the node sees); then the diagonals that cross
-    // two walls, with r_bd and Pbar* at the node: each traction wall's column
-    // of Pbar* is -s T* + K n, K at the wall the mean of the node's and the
-    // one beyond it, the off-diagonal entry the mean of both walls' values;
-    // a momentum wall (the mean j* of two) bounces back. (A rolled loop over
-    // eight links with the two-wall rule for each: 8.8 us per step on the 64 x
-    // 64 plate with a hole in FP64 with 16 x 16 windows, against 8.2.)
+    // Values the walls return to node i, into the slots its pull reads (m, H:
+    // as side). y walls alone take the fused kernel's form. The general form
+    // goes one side at a time, three links each, then over the diagonals that
+    // cross two walls: the off-diagonal entry of Pbar* is the mean of both
+    // walls' values, a momentum wall (the mean j* of two) bounces back. (A
+    // rolled loop over eight links with the two-wall rule for each: 8.8 us per
+    // step on the 64 x 64 plate with a hole in FP64 with 16 x 16 windows,
+    // against 8.2.)
     __device__ __forceinline__ void walls(int i, unsigned fl, const TC H[4], const TC m[4])
     {
         fl = opaque(fl);
-        wall_y<-1>(i, fl, H, m[0], m[1]);
-        wall_y<1>(i, fl, H, m[0], m[1]);
-        wall_x<-1>(i, fl, H, m[0], m[2]);
-        wall_x<1>(i, fl, H, m[0], m[2]);
+        if constexpr (GEN == WIN_YWALLS) {
+            const bool top = fl & YH;
+            const int g = top ? i + WW : i - WW;
+            const double val[2] = {top ? p.val[EDGE_YMAX][0] : p.val[EDGE_YMIN][0],
+                                   top ? p.val[EDGE_YMAX][1] : p.val[EDGE_YMIN][1]};
+            const TC fco[3] = {L.f[top ? 1 : 3][i], L.f[top ? 4 : 6][i], L.f[top ? 5 : 7][i]};
+            TC w[3];
+            wall_populations(top, top ? p.bc[EDGE_YMAX] : p.bc[EDGE_YMIN], fco, val, m[0], m[1],
+                             TC(0.5) * (L.k[1][i] + L.k[1][g]), TC(0.5) * (L.k[3][i] + L.k[3][g]), w);
+            // returned as 4, 7, 8 (top) or 2, 5, 6
+            L.f[top ? 3 : 1][g] = w[0];
+            L.f[top ? 6 : 4][top ? g + 1 : g - 1] = w[1];
+            L.f[top ? 7 : 5][top ? g - 1 : g + 1] = w[2];
+            return;
+        }
+        side<0, -1>(i, fl, H, m);
+        side<0, 1>(i, fl, H, m);
+        side<1, -1>(i, fl, H, m);
+        side<1, 1>(i, fl, H, m);
 #pragma unroll 1
         for (int o = 5; o < 9; ++o) {
             const int ox = o == 5 || o == 8 ? 1 : -1, oy = o < 7 ? 1 : -1;
@@ -347,8 +342,9 @@ struct Window {
                 const TC Pyy = -cy * TC(hole ? 0.0 : p.val[ey][1]) + TC(0.5) * (L.k[3][i] + ky3);
                 const TC Pxy = TC(0.5) * (qx1 + qy0);
                 const TC third = TC(1) / TC(3);
-                const TC trA = (Pxx - m[0] * third) + (Pyy - m[0] * third);
-                val = -fco + TC(2) * w * (m[0] + TC(4.5) * (TC(2) * (trA * third + cx * cy * Pxy)));
+                const TC axx = Pxx - m[0] * third, ayy = Pyy - m[0] * third;
+                const TC d = (axx + TC(2) * (cx * cy * Pxy)) + ayy;
+                val = -fco + TC(2) * w * (m[0] + TC(4.5) * (d - (axx + ayy) * third));
             }
             L.f[o < 7 ? o + 1 : o - 3][i + oy * WW + ox] = val;
         }
@@ -380,7 +376,7 @@ struct Window {
 
         const int ux = x0 - h + lx;
         int x = ux, bx = 0;
-        if (!GEN || perx) {
+        if (GEN != WIN_GENERAL || perx) {
             x = wrap(ux, nx);
         } else if (ux < 0) {
             x = 0, bx = -ux;
@@ -406,9 +402,9 @@ struct Window {
             if (GEN) {
                 if (bx | by) {
                     fl[k] = bx + by == 1 ? (unsigned)GHOST : 0u;
-                    if (perx && uy == -1) fl[k] |= BOTTOM;
+                    if (GEN == WIN_YWALLS && uy == -1) fl[k] |= BOTTOM;
                 } else {
-                    if (!perx) fl[k] |= (ux == 0 ? XL : 0u) | (ux == nx - 1 ? XH : 0u);
+                    if (GEN == WIN_GENERAL && !perx) fl[k] |= (ux == 0 ? XL : 0u) | (ux == nx - 1 ? XH : 0u);
                     if (!pery) fl[k] |= (uy == 0 ? YL : 0u) | (uy == ny - 1 ? YH : 0u);
                 }
             }
@@ -427,7 +423,7 @@ struct Window {
                 }
             }
         }
-        if (GEN && p.mask) {
+        if (GEN == WIN_GENERAL && p.mask) {
             bool any = false;
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -612,7 +608,7 @@ struct Window {
     }
 };
 
-template <class PR, int MODE, int WW, int WH, int K, bool GEN>
+template <class PR, int MODE, int WW, int WH, int K, int GEN>
 __global__ void __launch_bounds__(WW *WH / K) window_step_kernel(const GenParams p, const WinGrid g)
 {
     using W = Window<PR, MODE, WW, WH, K, GEN>;
@@ -725,7 +721,7 @@ inline WinChoice choose_window(int cls, bool gen, int nx, int ny, int reach, boo
     return best;
 }
 
-template <class PR, int MODE, bool GEN, int S = 0>
+template <class PR, int MODE, int GEN, int S = 0>
 hipError_t launch_window(const GenParams &p, const WinGrid &g, int shape, hipStream_t st)
 {
     if constexpr (S < kNumWinShapes) {
@@ -741,9 +737,9 @@ hipError_t launch_window(const GenParams &p, const WinGrid &g, int shape, hipStr
 }
 
 // Enqueue nsteps (1 or 2; 1 with j extrapolated) time steps with windows of
-// shape `shape`; scratch as for general_step.
+// shape `shape` built for `edges` (WIN_*); scratch as for general_step.
 template <class PR>
-hipError_t window_step(GenParams p, int shape, int nsteps, char *scratch, hipStream_t st)
+hipError_t window_step(GenParams p, int edges, int shape, int nsteps, char *scratch, hipStream_t st)
 {
     const int reach = p.pc ? win_reach<1>() : win_reach<0>();
     WinGrid g = win_grid(kWinShapes[shape], p.nx, p.ny, nsteps * reach + (FStore<typename PR::TF>::kDeviation ? 1 : 0),
@@ -759,15 +755,18 @@ hipError_t window_step(GenParams p, int shape, int nsteps, char *scratch, hipStr
         if (e != hipSuccess) return e;
         p.j_prev = scratch;
     }
-    const bool gen = p.mask || p.bc[EDGE_XMIN] != BC_PERIODIC || p.bc[EDGE_YMIN] != BC_PERIODIC;
-    if (p.pc) return gen ? launch_window<PR, 1, true>(p, g, shape, st) : launch_window<PR, 1, false>(p, g, shape, st);
-    return gen ? launch_window<PR, 0, true>(p, g, shape, st) : launch_window<PR, 0, false>(p, g, shape, st);
+    if (p.pc) return edges == WIN_GENERAL  ? launch_window<PR, 1, WIN_GENERAL>(p, g, shape, st)
+                     : edges == WIN_YWALLS ? launch_window<PR, 1, WIN_YWALLS>(p, g, shape, st)
+                                           : launch_window<PR, 1, WIN_PERIODIC>(p, g, shape, st);
+    return edges == WIN_GENERAL  ? launch_window<PR, 0, WIN_GENERAL>(p, g, shape, st)
+           : edges == WIN_YWALLS ? launch_window<PR, 0, WIN_YWALLS>(p, g, shape, st)
+                                 : launch_window<PR, 0, WIN_PERIODIC>(p, g, shape, st);
 }
 
-extern template hipError_t window_step<PrecF64>(GenParams, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF32>(GenParams, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF32U64>(GenParams, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF16>(GenParams, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecBF16>(GenParams, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecF64>(GenParams, int, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecF32>(GenParams, int, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecF32U64>(GenParams, int, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecF16>(GenParams, int, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecBF16>(GenParams, int, int, int, char *, hipStream_t);
 
 }  // namespace lbm
