@@ -115,6 +115,8 @@ struct lbm_solver {
     unsigned long long seed = 0;
     bool force_general = false;  // run the general step even without x walls
     bool fused_set = false;      // the caller chose the fused kernel or its launch shape
+    Shape pair_shape{};          // launch shape of two-step launches the library picks (plan_pairs)
+    int pair_for = -1;           // y edges it was planned for (0 periodic, 1 walls; -1: none)
     bool has_mask = false;       // holes (lbm_set_mask)
     std::vector<unsigned char> mask_host;  // host copy of the mask (1 material, 0 hole)
     bool tables_dirty = true;    // the general step's tile table and fused list need rebuilding
@@ -342,6 +344,32 @@ void plan_launch(lbm_solver *h)
     int n_segs = resident / probe.n_strips;
     n_segs = std::max(1, std::min(n_segs, h->ny / 16));
     h->shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, n_segs, h->spl);
+}
+
+// Whether the library runs a plate that the caller chose no launch shape for
+// two steps per launch, and its shape: 32- and 64-bit populations with the
+// predictor-corrector, one wave of resident blocks whatever the rows of a
+// segment. 128 threads (two or more blocks per compute unit, which cover each
+// other's barriers) up to the sizes where the narrower strips' halo columns
+// cost more: us per step with 128 / 256 threads, and with one step per launch
+// before, FP64 1400^2 74 / 77 (115), 1900^2 115 / 116 (190), 2999 x 2501 221 /
+// 208 (379); FP32 1400^2 36.0 / 38.5 (49), 1900^2 62.6 / 60.6 (101), 2999 x
+// 2501 120 / 113 (213); FP32_U64 1900^2 83 / 81 (121), 2999 x 2501 146 / 139
+// (229); between y walls FP64 2999 x 2501 255 / 239 (378), FP32 133 / 174
+// (214). FP32_U64 between y walls needs more registers than two waves per
+// SIMD have: one step per launch there.
+bool plan_pairs(lbm_solver *h)
+{
+    const bool walled = h->bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC;
+    if (max_steps_per_launch(h->prec, h->scheme) < 2 || (walled && h->prec == LBM_FP32_U64)) return false;
+    if (h->pair_for == (walled ? 1 : 0)) return true;
+    const double cut = h->prec == LBM_FP64 ? (walled ? 2.5e6 : 5e6) : walled ? 1e18 : 2.5e6;
+    const int block = (double)h->nx * h->ny < cut ? 128 : 256;
+    const Shape probe = make_shape(h->nx, h->ny, h->prec, h->scheme, block, 1, 2);
+    const int segs = std::max(1, std::min(resident_blocks(h, block, 2) / probe.n_strips, h->ny / 4));
+    h->pair_shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, segs, 2);
+    h->pair_for = walled ? 1 : 0;
+    return true;
 }
 
 }  // namespace
@@ -1037,16 +1065,24 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         return LBM_OK;
     }
     int64_t k = 0;
-    if (h->spl == 2) {
+    const bool pairs = !h->fused_set && nsteps >= 2 && plan_pairs(h);
+    if (h->spl == 2 || pairs) {
+        StepParams sp2 = sp;
+        const Shape &shape = pairs ? h->pair_shape : h->shape;
+        sp2.strip_w = shape.strip_w;
+        sp2.halo_a = shape.halo_a;
+        sp2.n_strips = shape.n_strips;
+        sp2.n_segs = shape.n_segs;
+        const int nb2 = shape.n_strips * shape.n_segs;
         for (; k + 2 <= nsteps; k += 2) {
-            sp.f_in = h->fptr(h->cur);
-            sp.u_in = h->uptr(h->cur);
-            sp.j_in = h->jptr(h->cur);
-            sp.f_out = h->fptr(h->cur ^ 1);
-            sp.u_out = h->uptr(h->cur ^ 1);
-            sp.j_out = h->jptr(h->cur ^ 1);
-            sp.step = h->steps;
-            HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2(sp, h->shape.block, nblocks, h->stream)));
+            sp2.f_in = h->fptr(h->cur);
+            sp2.u_in = h->uptr(h->cur);
+            sp2.j_in = h->jptr(h->cur);
+            sp2.f_out = h->fptr(h->cur ^ 1);
+            sp2.u_out = h->uptr(h->cur ^ 1);
+            sp2.j_out = h->jptr(h->cur ^ 1);
+            sp2.step = h->steps;
+            HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2(sp2, shape.block, nb2, h->stream)));
             h->cur ^= 1;
             h->steps += 2;
         }

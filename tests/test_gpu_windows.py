@@ -58,3 +58,16 @@ def test_windows_round_stochastically_as_the_fused_kernel(gpu, precision):
     b = _run(90, 64, precision, "pc", False, True, (9,), "stochastic")
     for x, y in zip(a[:3], b[:3]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("precision,walled,nx,ny", [("fp64", False, 1021, 777), ("fp64", True, 1021, 777),
+                                                    ("fp32", False, 1603, 900), ("fp32", True, 1603, 900),
+                                                    ("fp32u64", False, 1603, 900), ("fp32u64", True, 1603, 900),
+                                                    ("fp16", False, 1603, 900), ("fp16", True, 1603, 900)])
+def test_default_plan_of_larger_plates_equals_single_steps(gpu, precision, walled, nx, ny):
+    """Plates just beyond the windows' sizes: the library's own plan (two steps
+    per launch where it can, an odd remainder) against one step per launch."""
+    a = _run(nx, ny, precision, "pc", walled, False, (1, 4, 3))
+    b = _run(nx, ny, precision, "pc", walled, True, (8,))
+    for x, y in zip(a[:3], b[:3]):
+        assert np.array_equal(x, y)
