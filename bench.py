@@ -205,8 +205,8 @@ def copy_probe(mib: int, device):
 
 def general_source_hash() -> str:
     # the host code that splits the plate between the fused kernel and the
-    # 2D tiles decides the traffic too
-    return _code_hash(["general_kernels.hpp", "step_kernel.hpp", "lattice.hpp", "lbm_solid.hip"])
+    # windows decides the traffic too
+    return _code_hash(["window_kernel.hpp", "split_plan.hpp", "step_kernel.hpp", "lattice.hpp", "lbm_solid.hip"])
 
 
 def general_traffic_for(precision: str, n: int):
@@ -233,7 +233,7 @@ def bench_hole(args):
     at rest; tau/dt = 0.55, as the paper runs its Sec. 7 examples (reading
     Q24): at 0.8 the scheme itself diverges on this plate within a few
     hundred steps. It runs on the general step: the fused kernel for the
-    strips and rows clear of the walls and the hole, beside 2D tiles for the
+    strips and rows clear of the walls and the hole, beside windows for the
     rest."""
     import torch
 
@@ -276,7 +276,7 @@ def bench_hole(args):
         "config": {"workload": f"plate with a centred square hole (Sec. 7.2 geometry) on {n}x{n} nodes, hole "
                                f"{h}x{h}, all edges and the hole traction-free except 0.02 mu normal traction on "
                                "top and bottom, lam = mu = 1, tau/dt = 0.55, predictor-corrector; general step (fused "
-                               "kernel clear of walls and hole, 2D tiles for the rest); MLUPS counts material nodes",
+                               "kernel clear of walls and hole, windows for the rest); MLUPS counts material nodes",
                    "grid": [n, n], "material_sites": material, "precision": prec, "scheme": "pc",
                    "repeats": args.repeats, "window_ms": [round(w, 4) for w in windows_ms]},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
@@ -528,7 +528,7 @@ def main():
         "warmup": args.warmup, "ms_per_step": round(ms_step, 5), "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": DTYPE[prec], "data": "synthetic",
         "config": {"workload": wl["desc"], "grid": [nx, ny], "sites": sites, "precision": prec, "scheme": "pc",
-                   "tiling": ({"path": "general step (2D tiles, 512 threads)", "source": tiling_source} if general else
+                   "tiling": ({"path": "general step (2D windows)", "source": tiling_source} if general else
                               {"block": block, "n_segs": segs, "steps_per_launch": spl, "source": tiling_source}),
                    "repeats": args.repeats, "window_ms": [round(w, 4) for w in windows_ms],
                    "wall_s": round(wall, 4)},

@@ -3,7 +3,7 @@
 The step's results do not depend on how it is launched, only its speed does:
 the fused step kernel's shape (threads per block = columns per strip + halo,
 row segments per strip, one or two steps per launch), or the general step
-(2D tiles whose stages run in parallel, the faster one on small plates). For
+(2D windows whose stages run in parallel, the faster one on small plates). For
 a plate size, precision and scheme the tuner times a short run of each
 candidate with HIP events on the solver's stream, times the fastest few
 again over longer runs, and keeps the fastest of those.

@@ -69,7 +69,7 @@ __device__ __forceinline__ StepParams plate_step_params(const PlateDesc &pd, int
     sp.n_strips = pd.n_strips;
     sp.n_segs = pd.n_segs;
     sp.halo_a = pd.halo_a;
-    sp.x_lo = sp.x_end = 0;  // strips over the whole width
+    sp.x_lo = sp.x_end = sp.y_lo = sp.y_end = 0;  // the whole plate
     sp.flag = pd.flag;
     sp.step = step;
     sp.sr = pd.sr;
@@ -90,7 +90,7 @@ __global__ void __launch_bounds__(BLOCK)
         const PlateDesc &pd = plates[td.plate];
         if (k >= pd.nsteps) continue;  // uniform over the block
         const StepParams sp = plate_step_params(pd, (pd.parity0 + k) & 1, pd.step0 + k);
-        step_tile<PR, BLOCK, PC, WALLED>(sp, td.strip, td.seg, lds);
+        step_tile<PR, BLOCK, PC, WALLED>(sp, tile_geom(sp, td.strip, td.seg), lds);
     }
 }
 
@@ -114,9 +114,9 @@ __global__ void __launch_bounds__(BLOCK)
         if (left <= 0) continue;  // uniform over the block
         const StepParams sp = plate_step_params(pd, (pd.parity0 + k) & 1, pd.step0 + 2 * k);
         if (left >= 2)
-            step2_tile<PR, BLOCK, WALLED>(sp, td.strip, td.seg, lds[0], lds[1]);
+            step2_tile<PR, BLOCK, WALLED>(sp, tile_geom(sp, td.strip, td.seg), lds[0], lds[1]);
         else
-            step_tile<PR, BLOCK, true, WALLED>(sp, td.strip, td.seg, lds[0]);
+            step_tile<PR, BLOCK, true, WALLED>(sp, tile_geom(sp, td.strip, td.seg), lds[0]);
     }
 }
 

@@ -83,7 +83,6 @@ inline int stencil_halo(lbm_precision p, lbm_scheme s, int steps_per_launch)
 // Launch shape of one plate: column strips and row segments.
 struct Shape {
     int block, strip_w, n_strips, n_segs, halo_a;
-    int x_lo = 0, x_end = 0;  // strips over columns [x_lo, x_end) (x_end 0: the whole width)
 };
 
 // When the plate is wider than one block's reach, each strip's output width
@@ -214,13 +213,10 @@ struct Kernels {
     // The entry points below are defined out of the class (not inline), so
     // that each precision is instantiated in one object only.
     static hipError_t step(const StepParams &sp, int block, int nblocks, bool pc, hipStream_t st);
-    // one step over a tile list (256 threads per block; sp's shape is the
-    // 256-thread shape)
-    static hipError_t step_list(const StepParams &sp, const int *list, int n, bool pc, hipStream_t st);
-    // two predictor-corrector steps over a tile list (256 threads, the
-    // two-step shape); hipErrorInvalidConfiguration where the block's LDS
-    // does not fit
-    static hipError_t step2_list(const StepParams &sp, const int *list, int n, hipStream_t st);
+    // one step, or two predictor-corrector steps, over a tile list (256
+    // threads per block, sp.halo_a of them left of the output columns)
+    static hipError_t step_list(const StepParams &sp, const int4 *list, int n, bool pc, hipStream_t st);
+    static hipError_t step2_list(const StepParams &sp, const int4 *list, int n, hipStream_t st);
     // whether a two-step block of this many threads fits the LDS
     static bool step2_ok(int block, bool walled);
     // two predictor-corrector steps per launch
@@ -243,40 +239,25 @@ hipError_t Kernels<PR>::step(const StepParams &sp, int block, int nblocks, bool 
 }
 
 template <class PR>
-hipError_t Kernels<PR>::step_list(const StepParams &sp, const int *list, int n, bool pc, hipStream_t st)
+hipError_t Kernels<PR>::step_list(const StepParams &sp, const int4 *list, int n, bool pc, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    const bool w = sp.bc_lo != BC_PERIODIC;
-    if (pc) {
-        if (w)
-            hipLaunchKernelGGL((step_list_kernel<PR, 256, true, true>), dim3(n), dim3(256), 0, st, sp, list, n);
-        else
-            hipLaunchKernelGGL((step_list_kernel<PR, 256, true, false>), dim3(n), dim3(256), 0, st, sp, list, n);
-    } else {
-        if (w)
-            hipLaunchKernelGGL((step_list_kernel<PR, 256, false, true>), dim3(n), dim3(256), 0, st, sp, list, n);
-        else
-            hipLaunchKernelGGL((step_list_kernel<PR, 256, false, false>), dim3(n), dim3(256), 0, st, sp, list, n);
-    }
+    if (pc)
+        hipLaunchKernelGGL((step_list_kernel<PR, 256, true>), dim3(n), dim3(256), 0, st, sp, list, n);
+    else
+        hipLaunchKernelGGL((step_list_kernel<PR, 256, false>), dim3(n), dim3(256), 0, st, sp, list, n);
     return hipGetLastError();
 }
 
 template <class PR>
-hipError_t Kernels<PR>::step2_list(const StepParams &sp, const int *list, int n, hipStream_t st)
+hipError_t Kernels<PR>::step2_list(const StepParams &sp, const int4 *list, int n, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (sp.bc_lo != BC_PERIODIC) {
-        if constexpr (step2_fits<256, true>())
-            hipLaunchKernelGGL((step2_list_kernel<PR, 256, true>), dim3(n), dim3(256), 0, st, sp, list, n);
-        else
-            return hipErrorInvalidConfiguration;
-    } else {
-        if constexpr (step2_fits<256, false>())
-            hipLaunchKernelGGL((step2_list_kernel<PR, 256, false>), dim3(n), dim3(256), 0, st, sp, list, n);
-        else
-            return hipErrorInvalidConfiguration;
+    if constexpr (step2_fits<256, false>()) {
+        hipLaunchKernelGGL((step2_list_kernel<PR, 256>), dim3(n), dim3(256), 0, st, sp, list, n);
+        return hipGetLastError();
     }
-    return hipGetLastError();
+    return hipErrorInvalidConfiguration;
 }
 
 template <class PR>

@@ -13,9 +13,8 @@
 #include <string>
 #include <vector>
 
-#include "general_kernels.hpp"
 #include "host_common.hpp"
-#include "window_kernel.hpp"
+#include "split_plan.hpp"
 
 using namespace lbm;
 
@@ -25,28 +24,14 @@ struct Layout {
     StateLayout state;
     size_t staging, staging_bytes;
     size_t partials, small, total;
-    size_t scratch, total_walled;  // scratch of the general step (walls on the x edges)
-    size_t mask;                   // material mask [ny][nx] bytes, after the scratch
-    size_t tiles;                  // tile table of the general step (TILE_* bytes), after the mask
-    size_t flist;                  // fused-kernel tiles of the general step (3 ints each), after the tiles
-    size_t tlist;                  // the 2D tiles the general step launches (int each), after the fused list
-    // paired steps: the two-step fused list, the 2D tiles of the first step
-    // (the rest widened by one tile) and of the second (the rest), and a
-    // third copy of the state for the first step's output
-    size_t flist2, tlist_a, tlist_b;
-    size_t mid_f, mid_u, mid_j;
+    // walled workspace: a third buffer of j (the extrapolation variant), the material
+    // mask [ny][nx] bytes, and the lists of the split plans of one and two
+    // steps (split_plan.hpp)
+    size_t scratch, mask, list[2], total_walled;
 };
 
-size_t general_scratch(int nx, int ny, lbm_precision p)
-{
-    switch (p) {
-    case LBM_FP64: return general_scratch_bytes<PrecF64>(nx, ny);
-    case LBM_FP32: return general_scratch_bytes<PrecF32>(nx, ny);
-    case LBM_FP16_STORE: return general_scratch_bytes<PrecF16>(nx, ny);
-    case LBM_FP32_U64: return general_scratch_bytes<PrecF32U64>(nx, ny);
-    default: return general_scratch_bytes<PrecBF16>(nx, ny);
-    }
-}
+// Entries of a split plan's list (fused tiles and windows) there is room for.
+size_t list_capacity(int nx, int ny) { return 4096 + (size_t)nx * ny / 128; }
 
 Layout make_layout(int nx, int ny, lbm_precision p)
 {
@@ -62,19 +47,10 @@ Layout make_layout(int nx, int ny, lbm_precision p)
     off = align_up(off + 64 * sizeof(double));
     L.total = off;
     L.scratch = off;
-    L.mask = align_up(off + general_scratch(nx, ny, p));
-    L.tiles = align_up(L.mask + (size_t)nx * ny);
-    L.flist = align_up(L.tiles + max_tiles(nx, ny));
-    L.tlist = align_up(L.flist + 3 * sizeof(int) * max_tiles(nx, ny));
-    L.flist2 = align_up(L.tlist + sizeof(int) * max_tiles(nx, ny));
-    L.tlist_a = align_up(L.flist2 + 3 * sizeof(int) * max_tiles(nx, ny));
-    L.tlist_b = align_up(L.tlist_a + sizeof(int) * max_tiles(nx, ny));
-    const ElemSizes es = elem_sizes(p);
-    const size_t n = (size_t)nx * ny;
-    L.mid_f = align_up(L.tlist_b + sizeof(int) * max_tiles(nx, ny));
-    L.mid_u = align_up(L.mid_f + 9 * n * es.f);
-    L.mid_j = align_up(L.mid_u + 2 * n * es.u);
-    L.total_walled = align_up(L.mid_j + 2 * n * es.j);
+    L.mask = align_up(off + 2 * (size_t)nx * ny * elem_sizes(p).j);
+    L.list[0] = align_up(L.mask + (size_t)nx * ny);
+    L.list[1] = align_up(L.list[0] + sizeof(int4) * list_capacity(nx, ny));
+    L.total_walled = align_up(L.list[1] + sizeof(int4) * list_capacity(nx, ny));
     return L;
 }
 
@@ -98,6 +74,7 @@ struct lbm_solver {
     hipStream_t stream = nullptr;
     Layout L{};
     int cur = 0;  // copy holding the current state
+    int jslot = 0;  // buffer of the current j (j extrapolated)
     bool material = false, fields = false;
     double rho0 = 1, lam = 0, mu = 0, tau = 1;
     double body[2] = {0, 0};
@@ -115,20 +92,16 @@ struct lbm_solver {
     unsigned long long seed = 0;
     bool force_general = false;  // run the general step even without x walls
     bool fused_set = false;      // the caller chose the fused kernel or its launch shape
-    Shape pair_shape{};          // launch shape of two-step launches the library picks (plan_pairs)
-    int pair_for = -1;           // y edges it was planned for (0 periodic, 1 walls; -1: none)
+    Shape pair_shape{};          // launch shape of the library's own two-step launches (plan_pairs)
+    bool pair_for = false;       // it is planned
     bool has_mask = false;       // holes (lbm_set_mask)
     std::vector<unsigned char> mask_host;  // host copy of the mask (1 material, 0 hole)
-    bool tables_dirty = true;    // the general step's tile table and fused list need rebuilding
-    bool tables_built = false;   // the tile table in the workspace is valid
-    int n_flist = 0;             // entries of the fused list
-    int n_tlist = 0;             // entries of the 2D tile list
-    int n_flist2 = 0, n_tlist_a = 0, n_tlist_b = 0;  // paired steps (n_flist2 = 0: none)
-    Shape fshape2{};             // the two-step fused list's launch shape
-    Shape fshape{};              // the fused list's launch shape (256 threads, one step)
-    // The 2D tiles run on a second stream beside the fused share (forked
-    // from and joined back into the handle's stream each step or pair);
-    // created on first use, default priority.
+    // how launches of one and of two steps split the plate between the fused
+    // kernel and windows; rebuilt when the mask or the kind of an edge changes
+    SplitPlan split[2];
+    // The windows of a large split plate run on a second stream beside the
+    // fused share (forked from and joined back into the handle's stream each
+    // launch); created on first use, default priority.
     hipStream_t aux = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
     ~lbm_solver()
@@ -139,29 +112,36 @@ struct lbm_solver {
         if (aux) (void)hipStreamDestroy(aux);
     }
 
+    // plates that the fused kernel's walled form cannot run whole
     bool general() const
     {
         return force_general || has_mask || bc[LBM_EDGE_XMIN] != LBM_BC_PERIODIC || scheme == LBM_SCHEME_EXTRAP;
     }
-    // Whether windows (window_kernel.hpp) run the plate's steps in place of
-    // the fused kernel or of the general step's fused share: always where the
-    // caller asked for the general step or j is extrapolated; else, unless the
-    // caller chose the fused kernel or its shape, up to the plate size where
-    // the fused kernel's best launch shape caught up. us per step, windows
-    // against that: periodic FP64 700^2 31.9 / 31.8, FP32 1000^2 27.6 / 27.1,
-    // FP32_U64 1400^2 53 / 48, FP16 1400^2 65 / 61; y walls FP64 700^2 38 / 38,
-    // FP32 1000^2 33.9 / 34.1, FP32_U64 1000^2 41 / 38, FP16 1000^2 44.5 /
-    // 43.2; walls and holes FP64 1000^2 76 / 66, FP32 38 / 45, FP16 2000^2
-    // 178 / 149. Narrow plates go by their number of sites too.
+    // Whether windows (window_kernel.hpp) run the whole plate: where the caller
+    // asked for the general step; with j extrapolated unless a plate with walls
+    // is large enough for the periodic form to run most of it; else, unless the
+    // caller chose the fused kernel or its shape, up to the size where the
+    // fused kernel (with windows at walls and holes) caught up. us per step,
+    // windows / that: periodic FP64 700^2 31.9 / 31.8, FP32 1000^2 27.6 / 27.1,
+    // FP32_U64 1400^2 53 / 48, FP16 1400^2 65 / 61; y walls FP64 700^2 34 / 39,
+    // 1000^2 70 / 49, FP32 1000^2 33.8 / 34.1, FP32_U64 39 / 43, FP16 1400^2 73
+    // / 71; four walls FP64 500^2 33 / 38, 700^2 51 / 47, FP32 1000^2 38 / 37,
+    // FP32_U64 49 / 47, FP16 51 / 50. Narrow plates go by their sites too.
     bool windows() const
     {
-        if (scheme == LBM_SCHEME_EXTRAP || (force_general && !split_edges())) return true;
+        if (scheme == LBM_SCHEME_EXTRAP) return !walls() || (double)nx * ny <= 3e5;
+        if (force_general && !split_edges()) return true;
         if (fused_set && !split_edges()) return false;
         static const double limit[3][4] = {{5e5, 1.0e6, 1.2e6, 1.2e6},   // periodic: FP64, FP32, FP32_U64, 16-bit
-                                           {5e5, 1.0e6, 0.7e6, 1.0e6},   // y walls
-                                           {7e5, 1.2e6, 1.2e6, 2.4e6}};  // x walls or holes
+                                           {6e5, 1.0e6, 1.1e6, 1.8e6},   // y walls
+                                           {5e5, 1.0e6, 1.0e6, 1.0e6}};  // x walls or holes
         const int kind = split_edges() ? 2 : bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC ? 1 : 0;
         return (double)nx * ny <= limit[kind][win_class(prec)];
+    }
+    void drop_plans()
+    {
+        for (SplitPlan &p : split) p.built = false;
+        pair_for = false;
     }
     // any wall or hole
     bool walls() const { return split_edges() || bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC; }
@@ -171,15 +151,18 @@ struct lbm_solver {
     {
         return has_mask ? reinterpret_cast<const unsigned char *>(ws + L.mask) : nullptr;
     }
-    const unsigned char *tiles_ptr() const
-    {
-        return tables_built ? reinterpret_cast<const unsigned char *>(ws + L.tiles) : nullptr;
-    }
     std::string err;
 
     void *fptr(int c) const { return ws + L.state.f[c]; }
     void *uptr(int c) const { return ws + L.state.u[c]; }
-    void *jptr(int c) const { return ws + L.state.j[c]; }
+    // With j extrapolated a step reads j of the two states before it while it
+    // writes the next: three buffers take turns, jslot holding the current one
+    // and the one before it that of copy cur ^ 1.
+    void *jbuf(int k) const { return k % 3 == 2 ? ws + L.scratch : ws + L.state.j[k % 3]; }
+    void *jptr(int c) const
+    {
+        return scheme == LBM_SCHEME_EXTRAP ? jbuf(c == cur ? jslot : jslot + 2) : ws + L.state.j[c];
+    }
     unsigned *flag() const { return reinterpret_cast<unsigned *>(ws + L.small); }
     Units units() const { return Units{dx, rho0, lam, mu}; }
 
@@ -346,30 +329,116 @@ void plan_launch(lbm_solver *h)
     h->shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, n_segs, h->spl);
 }
 
-// Whether the library runs a plate that the caller chose no launch shape for
-// two steps per launch, and its shape: 32- and 64-bit populations with the
-// predictor-corrector, one wave of resident blocks whatever the rows of a
-// segment. 128 threads (two or more blocks per compute unit, which cover each
-// other's barriers) up to the sizes where the narrower strips' halo columns
-// cost more: us per step with 128 / 256 threads, and with one step per launch
-// before, FP64 1400^2 74 / 77 (115), 1900^2 115 / 116 (190), 2999 x 2501 221 /
-// 208 (379); FP32 1400^2 36.0 / 38.5 (49), 1900^2 62.6 / 60.6 (101), 2999 x
-// 2501 120 / 113 (213); FP32_U64 1900^2 83 / 81 (121), 2999 x 2501 146 / 139
-// (229); between y walls FP64 2999 x 2501 255 / 239 (378), FP32 133 / 174
-// (214). FP32_U64 between y walls needs more registers than two waves per
-// SIMD have: one step per launch there.
+// Threads per block of the library's own two-step launches over `sites` sites
+// of a periodic plate (or the part of a plate clear of walls): 128 (two or
+// more blocks per compute unit, which cover each other's barriers) up to the
+// sizes where the narrower strips' halo columns cost more; us per step with
+// 128 / 256 threads: FP64 1400^2 74 / 77, 1900^2 115 / 116, 2999 x 2501 221 /
+// 208; FP32 1400^2 36.0 / 38.5, 1900^2 62.6 / 60.6, 2999 x 2501 120 / 113;
+// FP32_U64 1900^2 83 / 81, 2999 x 2501 146 / 139.
+int pair_block(lbm_precision p, double sites) { return sites < (p == LBM_FP64 ? 5e6 : 2.5e6) ? 128 : 256; }
+
+// Launch shape of two steps per launch on a periodic plate that the caller
+// chose none for: one wave of resident blocks whatever the rows of a segment
+// (one step per launch before: FP64 1400^2 115 us per step, 2999 x 2501 379;
+// FP32 49, 213; FP32_U64 1900^2 121, 2999 x 2501 229).
 bool plan_pairs(lbm_solver *h)
 {
-    const bool walled = h->bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC;
-    if (max_steps_per_launch(h->prec, h->scheme) < 2 || (walled && h->prec == LBM_FP32_U64)) return false;
-    if (h->pair_for == (walled ? 1 : 0)) return true;
-    const double cut = h->prec == LBM_FP64 ? (walled ? 2.5e6 : 5e6) : walled ? 1e18 : 2.5e6;
-    const int block = (double)h->nx * h->ny < cut ? 128 : 256;
+    if (max_steps_per_launch(h->prec, h->scheme) < 2 || h->walls()) return false;
+    if (h->pair_for) return true;
+    const int block = pair_block(h->prec, (double)h->nx * h->ny);
     const Shape probe = make_shape(h->nx, h->ny, h->prec, h->scheme, block, 1, 2);
     const int segs = std::max(1, std::min(resident_blocks(h, block, 2) / probe.n_strips, h->ny / 4));
     h->pair_shape = make_shape(h->nx, h->ny, h->prec, h->scheme, block, segs, 2);
-    h->pair_for = walled ? 1 : 0;
+    h->pair_for = true;
     return true;
+}
+
+// Sites from which a split plate's windows run beside the fused share on a
+// second stream: below, forking and joining costs more than the overlap gives
+// (us per step, one stream / two: with a hole FP64 4096^2 484 / 437, 2000^2
+// 152 / 155; FP32_U64 271 / 267, 97 / 102; FP16 364 / 358, 122 / 132).
+constexpr double kBesideSites = 1e7;
+
+// Split of the plate between the fused kernel and windows for launches of
+// `steps` steps; false: the plate leaves the fused kernel no worthwhile share
+// (or the lists no room).
+hipError_t plan_split(lbm_solver *h, int steps)
+{
+    SplitPlan &p = h->split[steps - 1];
+    if (p.built) return hipSuccess;
+    p = SplitPlan{};
+    p.built = true;
+    const int nx = h->nx, ny = h->ny;
+    const SplitEdges e{nx, ny, h->bc[LBM_EDGE_XMIN] == LBM_BC_PERIODIC, h->bc[LBM_EDGE_YMIN] == LBM_BC_PERIODIC,
+                       stencil_halo(h->prec, h->scheme, steps), h->prec == LBM_FP64 ? 16 : 32};
+    const int reach = h->scheme == LBM_SCHEME_EXPLICIT ? win_reach<0>() : win_reach<1>();
+    const bool extrap = h->scheme == LBM_SCHEME_EXTRAP;
+    int mw = 0, mh = 0;
+    auto windows = [&](const std::vector<Rect> &rects, int edges, WinGrid &g, int &shape) {
+        const bool dev = deviation_storage(h->prec);
+        shape = choose_window(win_class(h->prec), edges, rects, reach, dev, steps, steps).shape;
+        const int hh = steps * reach + (dev ? 1 : 0);
+        mw = win_out(kWinShapes[shape].w, hh);
+        mh = win_out(kWinShapes[shape].h, hh);
+        g.nsteps = steps;
+    };
+    const int rest = h->general() ? WIN_GENERAL : WIN_YWALLS;
+    if (!h->has_mask) {
+        const Rect box = split_box(e);
+        if (box.w < kSplitMinCols || box.h < kSplitMinRows) return hipSuccess;
+        const int block = steps == 2 ? pair_block(h->prec, (double)box.w * box.h) : 256;
+        p.shape = make_shape(nx, ny, h->prec, h->scheme, block, 1, steps);
+        p.box = box;
+        p.shape.n_strips = (box.w + p.shape.strip_w - 1) / p.shape.strip_w;
+        p.shape.n_segs = std::max(1, std::min(resident_blocks(h, block, steps, 0) / p.shape.n_strips, box.h / 8));
+        auto regions = [&](const std::vector<Rect> &rects, WinGrid &g) {
+            for (const Rect &r : rects) {
+                g.reg[g.n_regions] = win_region(r, mw, mh, g.nb);
+                g.nb += win_blocks(g.reg[g.n_regions++]);
+            }
+        };
+        const std::vector<Rect> rects = split_frame(e, box);
+        windows(rects, rest, p.win, p.win_shape);
+        regions(rects, p.win);
+        if (extrap) {
+            windows({box}, WIN_PERIODIC, p.inner, p.inner_shape);
+            regions({box}, p.inner);
+        }
+        p.use = true;
+        return hipSuccess;
+    }
+    p.shape = make_shape(nx, ny, h->prec, h->scheme, 256, 1, steps);
+    std::vector<int4> list;
+    std::vector<Rect> rects;
+    split_mask(e, h->mask_host.data(), extrap ? nx : p.shape.strip_w, extrap ? 1 : resident_blocks(h, 256, steps, 0),
+               list, rects);
+    if (list.empty()) return hipSuccess;
+    if (extrap) {
+        std::vector<Rect> clear;
+        for (const int4 &t : list) clear.push_back(Rect{t.x, t.z, t.y, t.w - t.z});
+        list.clear();
+        windows(clear, WIN_PERIODIC, p.inner, p.inner_shape);
+        split_windows(nx, h->mask_host.data(), clear, mw, mh, list);
+        p.inner.nb = (int)list.size();
+    }
+    p.n_fused = (int)list.size();
+    windows(rects, rest, p.win, p.win_shape);
+    split_windows(nx, h->mask_host.data(), rects, mw, mh, list);
+    if (list.size() > list_capacity(nx, ny)) return hipSuccess;
+    p.win.nb = (int)list.size() - p.n_fused;
+    hipError_t err = hipMemcpyAsync(h->ws + h->L.list[steps - 1], list.data(), sizeof(int4) * list.size(),
+                                    hipMemcpyHostToDevice, h->stream);
+    if (!err) err = hipStreamSynchronize(h->stream);
+    if (err) {
+        p.built = false;
+        return err;
+    }
+    p.fused_list = reinterpret_cast<const int4 *>(h->ws + h->L.list[steps - 1]);
+    p.win.list = p.fused_list + p.n_fused;
+    if (extrap) p.inner.list = p.fused_list;
+    p.use = true;
+    return hipSuccess;
 }
 
 }  // namespace
@@ -473,7 +542,7 @@ lbm_status lbm_set_boundary(lbm_solver *h, lbm_edge e, lbm_bc bc, const double v
         // the opposite edge stops being periodic: it becomes a wall at rest until set
         h->set_edge(other, LBM_BC_DIRICHLET_J, 0.0, 0.0);
     }
-    if ((h->bc[e] == LBM_BC_PERIODIC) != (bc == LBM_BC_PERIODIC)) h->tables_dirty = true;
+    if ((h->bc[e] == LBM_BC_PERIODIC) != (bc == LBM_BC_PERIODIC)) h->drop_plans();
     h->set_edge(e, bc, bc == LBM_BC_PERIODIC ? 0.0 : value[0], bc == LBM_BC_PERIODIC ? 0.0 : value[1]);
     refit_two_step(h);
     HIP_TRY(h, h->refit_scale());
@@ -527,7 +596,7 @@ lbm_status lbm_set_mask(lbm_solver *h, const unsigned char *solid)
     if (!solid) {
         h->has_mask = false;
         h->mask_host.clear();
-        h->tables_dirty = true;
+        h->drop_plans();
         return LBM_OK;
     }
     if (h->ws_bytes < h->L.total_walled)
@@ -564,7 +633,7 @@ lbm_status lbm_set_mask(lbm_solver *h, const unsigned char *solid)
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->mask_host.swap(dev);
     h->has_mask = true;
-    h->tables_dirty = true;
+    h->drop_plans();
     return LBM_OK;
 }
 
@@ -618,6 +687,7 @@ lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0)
     if (!u0 || !v0) return fail(h, LBM_ERR_ARG, "u0 or v0 is NULL");
     if (!h->material) return fail(h, LBM_ERR_STATE, "set the material before the fields");
     h->cur = 0;
+    h->jslot = 0;
     for (auto &w : h->uwb) w[0] = w[1] = 0.0;  // every wall starts undisplaced
     double scale = 1.0;
     bool nonfinite = false;
@@ -634,256 +704,6 @@ lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0)
     h->fields = true;
     return LBM_OK;
 }
-
-namespace {
-
-// The general step's tables, built on the host when the mask or the edges
-// change. The tile table marks each 2D tile whose window holds a hole node,
-// that holds a material node, and that the fused kernel computes instead.
-// The fused list: on a plate with x walls or holes, the tiles of the fused
-// step kernel (256-thread strips, row runs aligned to the 2D tiles' rows)
-// whose outputs lie farther than the stencil's reach from every wall and
-// hole. There the fused kernel's periodic arithmetic is the general rules'
-// arithmetic, and it runs those sites at the fused kernel's rate.
-hipError_t build_general_tables(lbm_solver *h)
-{
-    const int nx = h->nx, ny = h->ny;
-    const bool perx = h->bc[LBM_EDGE_XMIN] == LBM_BC_PERIODIC, pery = h->bc[LBM_EDGE_YMIN] == LBM_BC_PERIODIC;
-    const bool pc = h->scheme != LBM_SCHEME_EXPLICIT;
-    int tw = 0, th = 0, ru = 0;
-    switch (h->prec) {
-    case LBM_FP64: tile_shape<PrecF64>(pc, tw, th, ru); break;
-    case LBM_FP32: tile_shape<PrecF32>(pc, tw, th, ru); break;
-    case LBM_FP16_STORE: tile_shape<PrecF16>(pc, tw, th, ru); break;
-    case LBM_FP32_U64: tile_shape<PrecF32U64>(pc, tw, th, ru); break;
-    default: tile_shape<PrecBF16>(pc, tw, th, ru); break;
-    }
-    const int mg = stencil_halo(h->prec, h->scheme, 1);
-    // hole counts of boxes: per-row prefix sums over the rows and columns
-    // within max(ru, mg) of the plate (wrapped across periodic edges; beyond
-    // a wall there are no holes)
-    const int e = std::max(ru, mg);
-    const int W = nx + 2 * e, Hh = ny + 2 * e;
-    std::vector<uint32_t> pre;
-    const bool any_mask = h->has_mask;
-    if (any_mask) {
-        pre.assign((size_t)Hh * (W + 1), 0u);
-        const unsigned char *m = h->mask_host.data();
-        for (int r = 0; r < Hh; ++r) {
-            int y = r - e;
-            bool row_in = true;
-            if (y < 0 || y >= ny) {
-                if (pery) y = ((y % ny) + ny) % ny;
-                else row_in = false;
-            }
-            uint32_t *pr = pre.data() + (size_t)r * (W + 1);
-            for (int c = 0; c < W; ++c) {
-                int x = c - e;
-                bool in = row_in;
-                if (x < 0 || x >= nx) {
-                    if (perx) x = ((x % nx) + nx) % nx;
-                    else in = false;
-                }
-                pr[c + 1] = pr[c] + ((in && m[(size_t)y * nx + x] == 0) ? 1u : 0u);
-            }
-        }
-    }
-    // holes in [x0, x1) x [y0, y1), plate coordinates within e of the plate
-    auto holes_in = [&](int x0, int x1, int y0, int y1) -> bool {
-        if (!any_mask) return false;
-        x0 = std::max(x0, -e) + e, x1 = std::min(x1, nx + e) + e;
-        y0 = std::max(y0, -e) + e, y1 = std::min(y1, ny + e) + e;
-        for (int r = y0; r < y1; ++r) {
-            const uint32_t *pr = pre.data() + (size_t)r * (W + 1);
-            if (pr[x1] != pr[x0]) return true;
-        }
-        return false;
-    };
-    const int nbx = (nx + tw - 1) / tw, nby = (ny + th - 1) / th;
-    std::vector<unsigned char> tiles((size_t)nbx * nby, 0);
-    for (int ty = 0; ty < nby; ++ty)
-        for (int tx = 0; tx < nbx; ++tx) {
-            const int x0 = tx * tw, y0 = ty * th;
-            const int x1 = std::min(nx, x0 + tw), y1 = std::min(ny, y0 + th);
-            unsigned char f = 0;
-            // material: fewer hole nodes than nodes in the tile
-            if (!any_mask) {
-                f = TILE_MATERIAL;
-            } else {
-                uint32_t n = 0;
-                for (int r = y0 + e; r < y1 + e; ++r) {
-                    const uint32_t *pr = pre.data() + (size_t)r * (W + 1);
-                    n += pr[x1 + e] - pr[x0 + e];
-                }
-                if (n < (uint32_t)((x1 - x0) * (y1 - y0))) f = TILE_MATERIAL;
-            }
-            if (holes_in(x0 - ru, x0 + tw + ru, y0 - ru, y0 + th + ru)) f |= TILE_HOLES;
-            tiles[(size_t)ty * nbx + tx] = f;
-        }
-    // fused-kernel entries of a launch of spl steps: (strip, row run) pairs
-    // whose outputs lie farther than the launch's stencil reach from x walls
-    // and holes; `mark` receives the 2D tiles they cover
-    auto fused_list = [&](int spl, int runs, Shape &fs, std::vector<unsigned char> &mark) {
-        std::vector<int> list;
-        mark.assign(tiles.size(), 0);
-        if (h->scheme == LBM_SCHEME_EXTRAP || !(any_mask || !perx)) return list;
-        fs = make_shape(nx, ny, h->prec, h->scheme, 256, 1, spl);
-        const int reach = stencil_halo(h->prec, h->scheme, spl);
-        // row runs of at most seg_rows rows: about `runs` per strip
-        const int seg_rows = std::max(th, (ny / runs) / th * th);
-        // a strip's columns start on a 2D tile's column (strips are a
-        // multiple of 32 columns wide, or the whole plate)
-        if (!(fs.n_strips == 1 || fs.strip_w % tw == 0)) return list;
-        // with x walls the strips start at the first tile column beyond the
-        // reach from the wall and end at the last one before the far wall,
-        // so the 2D tiles keep one tile column at each wall, not a strip
-        int n_st = fs.n_strips;
-        if (!perx) {
-            fs.x_lo = (reach + tw - 1) / tw * tw;
-            fs.x_end = (nx - reach) / tw * tw;
-            n_st = fs.x_end > fs.x_lo ? (fs.x_end - fs.x_lo + fs.strip_w - 1) / fs.strip_w : 0;
-        }
-        const int xe = fs.x_end > 0 ? fs.x_end : nx;
-        // likewise the row runs stay a tile row clear of y walls: no output
-        // of the fused share then depends on a wall rule or a ghost row, and
-        // it runs the fused kernel's periodic form (fewer registers and LDS
-        // bytes than the walled one), leaving the rows at y walls to the tiles
-        const int ylo = pery ? 0 : (reach + th - 1) / th * th;
-        const int yend = pery ? ny : (ny - reach) / th * th;
-        for (int st = 0; st < n_st; ++st) {
-            const int x0 = fs.x_lo + st * fs.strip_w, x1 = std::min(xe, x0 + fs.strip_w);
-            if (!perx && (x0 - reach < 0 || x1 + reach > nx)) continue;
-            int run0 = -1;
-            for (int ty = 0; ty <= nby; ++ty) {
-                const bool clean = ty < nby && ty * th >= ylo && std::min(ny, ty * th + th) <= yend &&
-                                   !holes_in(x0 - reach, x1 + reach, ty * th - reach,
-                                             std::min(ny, ty * th + th) + reach);
-                if (clean && run0 < 0) run0 = ty;
-                if (!clean && run0 >= 0) {
-                    const int ya = run0 * th, yb = std::min(ny, ty * th);
-                    for (int a = ya; a < yb; a += seg_rows) {
-                        list.push_back(st);
-                        list.push_back(a);
-                        list.push_back(std::min(yb, a + seg_rows));
-                    }
-                    for (int t = run0; t < ty; ++t)
-                        for (int tx = x0 / tw; tx < (x1 + tw - 1) / tw; ++tx) mark[(size_t)t * nbx + tx] = 1;
-                    run0 = -1;
-                }
-            }
-        }
-        return list;
-    };
-    // The fused grid is sized to one wave of resident blocks of its periodic
-    // form: from 26 row runs per strip (as the default plan's segments of a
-    // periodic plate) down until the list fits; a block that waits for a
-    // second wave would double the share's time.
-    auto fused_fit = [&](int spl, Shape &fs, std::vector<unsigned char> &mark) {
-        const int slots = resident_blocks(h, 256, spl, 0);
-        int runs = 26;
-        for (;;) {
-            std::vector<int> list = fused_list(spl, runs, fs, mark);
-            const int n = (int)(list.size() / 3);
-            if (slots <= 0 || n <= slots || runs == 1) return list;
-            runs = std::max(1, std::min(runs - 1, (int)((long long)runs * slots / n)));
-        }
-    };
-    std::vector<unsigned char> mark1, mark2;
-    const std::vector<int> list = fused_fit(1, h->fshape, mark1);
-    for (size_t t = 0; t < tiles.size(); ++t)
-        if (mark1[t]) tiles[t] |= TILE_FUSED;
-    // the 2D tiles to launch: those with material that the fused kernel does
-    // not compute, in row-major order (the kernel deals them to the XCDs in
-    // equal runs)
-    std::vector<int> tl;
-    for (size_t t = 0; t < tiles.size(); ++t)
-        if ((tiles[t] & TILE_MATERIAL) && !(tiles[t] & TILE_FUSED)) tl.push_back((int)t);
-    // Paired steps: the two-step fused kernel over the strips clear of walls
-    // and holes by two steps' reach; the 2D tiles advance the rest in two
-    // launches, the first over the rest widened by one tile (at least the
-    // one-step reach in each direction) into a third state copy, the second
-    // from it over the rest.
-    // The fused share runs the periodic form, whose two-step block leaves
-    // room for a second one on a compute unit. On the 4096² plate with a
-    // hole, paired steps take 0.576 ms per step in FP64, 0.329 in FP32 and
-    // 0.429 in FP32 with a double displacement, against 0.534 one step at a
-    // time in the last (16-bit storage has no two-step kernel).
-    std::vector<int> list2, tla, tlb;
-    bool pair = false;
-    if (h->scheme == LBM_SCHEME_PC && th >= mg && tw >= mg) {
-        if (h->prec == LBM_FP64) pair = Kernels<PrecF64>::step2_ok(256, false);
-        if (h->prec == LBM_FP32) pair = Kernels<PrecF32>::step2_ok(256, false);
-        if (h->prec == LBM_FP32_U64) pair = Kernels<PrecF32U64>::step2_ok(256, false);
-    }
-    if (pair) {
-        list2 = fused_fit(2, h->fshape2, mark2);
-        std::vector<unsigned char> rest(tiles.size(), 0), wide(tiles.size(), 0);
-        for (size_t t = 0; t < tiles.size(); ++t) rest[t] = (tiles[t] & TILE_MATERIAL) && !mark2[t];
-        // nodes between [a0, a1) and [b0, b1) on a line or a ring of n nodes
-        auto gap = [](int a0, int a1, int b0, int b1, int n, bool per) {
-            int best = 1 << 30;
-            for (int sh = per ? -n : 0; sh <= (per ? n : 0); sh += n ? n : 1) {
-                const int c0 = b0 + sh, c1 = b1 + sh;
-                const int g = c0 >= a1 ? c0 - a1 + 1 : (a0 >= c1 ? a0 - c1 + 1 : 0);
-                best = std::min(best, g);
-                if (!per) break;
-            }
-            return best;
-        };
-        // the first launch covers every tile with a node within the
-        // one-step reach of a rest tile (two tiles around suffice: tiles are
-        // at least that reach wide, the ragged last one aside)
-        for (int ty = 0; ty < nby; ++ty)
-            for (int tx = 0; tx < nbx; ++tx) {
-                if (!rest[(size_t)ty * nbx + tx]) continue;
-                const int ax0 = tx * tw, ax1 = std::min(nx, ax0 + tw), ay0 = ty * th, ay1 = std::min(ny, ay0 + th);
-                for (int dy = -2; dy <= 2; ++dy)
-                    for (int dx = -2; dx <= 2; ++dx) {
-                        int ux = tx + dx, uy = ty + dy;
-                        if (ux < 0 || ux >= nbx) {
-                            if (!perx) continue;
-                            ux = (ux % nbx + nbx) % nbx;
-                        }
-                        if (uy < 0 || uy >= nby) {
-                            if (!pery) continue;
-                            uy = (uy % nby + nby) % nby;
-                        }
-                        const int bx0 = ux * tw, bx1 = std::min(nx, bx0 + tw);
-                        const int by0 = uy * th, by1 = std::min(ny, by0 + th);
-                        if (gap(ax0, ax1, bx0, bx1, nx, perx) <= mg && gap(ay0, ay1, by0, by1, ny, pery) <= mg)
-                            wide[(size_t)uy * nbx + ux] = 1;
-                    }
-            }
-        for (size_t t = 0; t < tiles.size(); ++t) {
-            if (wide[t] && (tiles[t] & TILE_MATERIAL)) tla.push_back((int)t);
-            if (rest[t]) tlb.push_back((int)t);
-        }
-        if (list2.empty()) tla.clear(), tlb.clear();
-    }
-    hipError_t err = hipMemcpyAsync(h->ws + h->L.tiles, tiles.data(), tiles.size(), hipMemcpyHostToDevice,
-                                    h->stream);
-    auto up = [&](size_t off, const std::vector<int> &v) {
-        if (!err && !v.empty())
-            err = hipMemcpyAsync(h->ws + off, v.data(), sizeof(int) * v.size(), hipMemcpyHostToDevice, h->stream);
-    };
-    up(h->L.flist, list);
-    up(h->L.tlist, tl);
-    up(h->L.flist2, list2);
-    up(h->L.tlist_a, tla);
-    up(h->L.tlist_b, tlb);
-    if (!err) err = hipStreamSynchronize(h->stream);
-    if (err) return err;
-    h->n_flist = (int)(list.size() / 3);
-    h->n_tlist = (int)tl.size();
-    h->n_flist2 = (int)(list2.size() / 3);
-    h->n_tlist_a = (int)tla.size();
-    h->n_tlist_b = (int)tlb.size();
-    h->tables_built = true;
-    h->tables_dirty = false;
-    return hipSuccess;
-}
-
-}  // namespace
 
 lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
 {
@@ -911,8 +731,24 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     sp.seed = h->seed;
     const int nblocks = h->shape.n_strips * h->shape.n_segs;
     const bool pc = h->scheme == LBM_SCHEME_PC;
-    const bool windows = h->windows();
-    if (windows || h->general()) {
+    auto advance = [&](auto &p) {  // state pointers and index of the next launch
+        p.f_in = h->fptr(h->cur);
+        p.u_in = h->uptr(h->cur);
+        p.j_in = h->jptr(h->cur);
+        p.f_out = h->fptr(h->cur ^ 1);
+        p.u_out = h->uptr(h->cur ^ 1);
+        p.j_out = h->jptr(h->cur ^ 1);
+        p.step = h->steps;
+    };
+    auto done = [&](int n) {
+        h->cur ^= 1;
+        h->jslot = (h->jslot + 1) % 3;
+        h->steps += n;
+    };
+    const bool whole_windows = h->windows();
+    const bool split = !whole_windows && h->walls() && (h->split_edges() || h->scheme == LBM_SCHEME_EXTRAP || !h->fused_set);
+    int64_t k = 0;
+    if (whole_windows || split) {
         GenParams gp{};
         gp.nx = h->nx;
         gp.ny = h->ny;
@@ -942,129 +778,90 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         gp.pc = h->scheme == LBM_SCHEME_EXTRAP ? 2 : (pc ? 1 : 0);
         gp.flag = sp.flag;
         gp.mask = h->mask_ptr();
-        if (windows) {
-            const int reach = pc || gp.pc ? win_reach<1>() : win_reach<0>();
-            const bool gen = edges != WIN_PERIODIC;
-            auto choose = [&](int max_steps) {
-                return choose_window(win_class(h->prec), gen, h->nx, h->ny, reach, deviation_storage(h->prec),
-                                     max_steps);
-            };
-            WinChoice c = choose(nsteps >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
-            for (int64_t k = 0; k < nsteps; k += c.steps) {
-                if (k + c.steps > nsteps) c = choose(1);  // an odd last step
-                gp.f_in = h->fptr(h->cur);
-                gp.u_in = h->uptr(h->cur);
-                gp.j_in = h->jptr(h->cur);
-                gp.f_out = h->fptr(h->cur ^ 1);
-                gp.u_out = h->uptr(h->cur ^ 1);
-                gp.j_out = h->jptr(h->cur ^ 1);
-                gp.step = h->steps;
-                HIP_TRY(h, LBM_DISPATCH(h->prec, window_step<PR>(gp, edges, c.shape, c.steps,
-                                                                 h->ws + h->L.scratch, h->stream)));
-                h->cur ^= 1;
-                h->steps += c.steps;
+        auto windows = [&](const WinGrid &g, int shape, int form, hipStream_t st) {
+            return LBM_DISPATCH(h->prec, window_step<PR>(gp, g, form, shape, st));
+        };
+        auto next = [&]() {
+            advance(gp);
+            if (gp.pc == 2) {  // j of the step before, and the third buffer
+                gp.j_prev = gp.j_out;
+                gp.j_out = h->jbuf(h->jslot + 1);
+            }
+        };
+        if (split) {
+            // The fused kernel's periodic form over the part of the plate
+            // clear of walls and holes, windows over the rest: both read the
+            // state of step n and write disjoint sites of the new one.
+            for (int n = max_steps_per_launch(h->prec, h->scheme); n >= 1; --n) {
+                if (nsteps - k < n) continue;
+                // y walls alone, one step: the fused kernel's walled form (below)
+                if (n == 1 && !h->split_edges() && gp.pc != 2) continue;
+                HIP_TRY(h, plan_split(h, n));
+                const SplitPlan &p = h->split[n - 1];
+                if (!p.use) continue;
+                StepParams fp = sp;
+                fp.bc_lo = fp.bc_hi = BC_PERIODIC;
+                fp.strip_w = p.shape.strip_w;
+                fp.halo_a = p.shape.halo_a;
+                fp.n_strips = p.shape.n_strips;
+                fp.n_segs = p.shape.n_segs;
+                fp.x_lo = p.box.x;
+                fp.x_end = p.box.x + p.box.w;
+                fp.y_lo = p.box.y;
+                fp.y_end = p.box.y + p.box.h;
+                const int nb = p.shape.n_strips * p.shape.n_segs;
+                const bool beside = h->split_edges() && (double)h->nx * h->ny >= kBesideSites;
+                if (beside && !h->aux) {
+                    HIP_TRY(h, hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
+                    HIP_TRY(h, hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
+                    HIP_TRY(h, hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
+                }
+                for (; k + n <= nsteps; k += n) {
+                    advance(fp);
+                    next();
+                    if (beside) {
+                        HIP_TRY(h, hipEventRecord(h->fork, h->stream));
+                        HIP_TRY(h, hipStreamWaitEvent(h->aux, h->fork, 0));
+                    }
+                    if (p.inner.nb > 0)
+                        HIP_TRY(h, windows(p.inner, p.inner_shape, WIN_PERIODIC, h->stream));
+                    else if (p.fused_list)
+                        HIP_TRY(h, n == 2 ? LBM_DISPATCH(h->prec, Kernels<PR>::step2_list(fp, p.fused_list, p.n_fused, h->stream))
+                                          : LBM_DISPATCH(h->prec, Kernels<PR>::step_list(fp, p.fused_list, p.n_fused, pc, h->stream)));
+                    else
+                        HIP_TRY(h, n == 2 ? LBM_DISPATCH(h->prec, Kernels<PR>::step2(fp, p.shape.block, nb, h->stream))
+                                          : LBM_DISPATCH(h->prec, Kernels<PR>::step(fp, p.shape.block, nb, pc, h->stream)));
+                    HIP_TRY(h, windows(p.win, p.win_shape, edges, beside ? h->aux : h->stream));
+                    if (beside) {
+                        HIP_TRY(h, hipEventRecord(h->join, h->aux));
+                        HIP_TRY(h, hipStreamWaitEvent(h->stream, h->join, 0));
+                    }
+                    done(n);
+                }
+            }
+        }
+        if (whole_windows || h->split_edges() || gp.pc == 2) {
+            const std::vector<Rect> plate = {Rect{0, 0, h->nx, h->ny}};
+            const int reach = gp.pc ? win_reach<1>() : win_reach<0>();
+            const bool dev = deviation_storage(h->prec);
+            while (k < nsteps) {
+                const WinChoice c = choose_window(win_class(h->prec), edges, plate, reach, dev, 1,
+                                                  nsteps - k >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
+                const int hh = c.steps * reach + (dev ? 1 : 0);
+                WinGrid g{};
+                g.nsteps = c.steps;
+                g.n_regions = 1;
+                g.reg[0] = win_region(plate[0], win_out(kWinShapes[c.shape].w, hh), win_out(kWinShapes[c.shape].h, hh), 0);
+                g.nb = win_blocks(g.reg[0]);
+                for (; k + c.steps <= nsteps; k += c.steps) {
+                    next();
+                    HIP_TRY(h, windows(g, c.shape, edges, h->stream));
+                    done(c.steps);
+                }
             }
             return LBM_OK;
         }
-        if (h->tables_dirty && h->ws_bytes >= h->L.total_walled) HIP_TRY(h, build_general_tables(h));
-        gp.tiles = h->tiles_ptr();
-        // without holes and without a fused share the table marks every
-        // tile as material and nothing else: go without it, so that small
-        // plates may take the two-row tiles
-        if (gp.tiles && !h->has_mask && h->n_flist == 0 && h->n_flist2 == 0) gp.tiles = nullptr;
-        gp.tlist = gp.tiles ? reinterpret_cast<const int *>(h->ws + h->L.tlist) : nullptr;
-        gp.n_tlist = gp.tiles ? h->n_tlist : 0;
-        // the fused kernel's share: the tiles clear of walls and holes (on
-        // the handle's stream, the 2D tiles beside it on the aux stream)
-        const int nf = gp.tiles ? h->n_flist : 0;
-        if ((nf > 0 || (gp.tiles && h->n_flist2 > 0)) && !h->aux) {
-            HIP_TRY(h, hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
-            HIP_TRY(h, hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
-            HIP_TRY(h, hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
-        }
-        const int *flist = reinterpret_cast<const int *>(h->ws + h->L.flist);
-        StepParams fp = sp;
-        fp.strip_w = h->fshape.strip_w;
-        fp.halo_a = h->fshape.halo_a;
-        fp.n_strips = h->fshape.n_strips;
-        fp.x_lo = h->fshape.x_lo;
-        fp.x_end = h->fshape.x_end;
-        fp.n_segs = 1;
-        fp.bc_lo = fp.bc_hi = BC_PERIODIC;  // the fused share is clear of y walls: periodic form
-        int64_t k = 0;
-        // paired steps: the two-step fused kernel on the handle's stream; on
-        // the aux stream the 2D tiles' first step (widened rest) into the
-        // third state copy, then their second step (rest) from it. The fused
-        // grid is one wave of resident blocks, so it is enqueued first: tile
-        // blocks holding compute units when it dispatches would push part of
-        // it into a second wave (0.86 against 0.49 ms per pair on the 4096²
-        // plate with a hole).
-        const int nf2 = gp.tiles ? h->n_flist2 : 0;
-        if (nf2 > 0) {
-            const int *flist2 = reinterpret_cast<const int *>(h->ws + h->L.flist2);
-            StepParams fp2 = sp;
-            fp2.strip_w = h->fshape2.strip_w;
-            fp2.halo_a = h->fshape2.halo_a;
-            fp2.n_strips = h->fshape2.n_strips;
-            fp2.x_lo = h->fshape2.x_lo;
-            fp2.x_end = h->fshape2.x_end;
-            fp2.n_segs = 1;
-            fp2.bc_lo = fp2.bc_hi = BC_PERIODIC;
-            GenParams ga = gp, gb = gp;
-            ga.tlist = reinterpret_cast<const int *>(h->ws + h->L.tlist_a);
-            ga.n_tlist = h->n_tlist_a;
-            gb.tlist = reinterpret_cast<const int *>(h->ws + h->L.tlist_b);
-            gb.n_tlist = h->n_tlist_b;
-            ga.f_out = h->ws + h->L.mid_f;
-            ga.u_out = h->ws + h->L.mid_u;
-            ga.j_out = h->ws + h->L.mid_j;
-            gb.f_in = ga.f_out;
-            gb.u_in = ga.u_out;
-            gb.j_in = ga.j_out;
-            for (; k + 2 <= nsteps; k += 2) {
-                fp2.f_in = ga.f_in = h->fptr(h->cur);
-                fp2.u_in = ga.u_in = h->uptr(h->cur);
-                fp2.j_in = ga.j_in = h->jptr(h->cur);
-                fp2.f_out = gb.f_out = h->fptr(h->cur ^ 1);
-                fp2.u_out = gb.u_out = h->uptr(h->cur ^ 1);
-                fp2.j_out = gb.j_out = h->jptr(h->cur ^ 1);
-                fp2.step = ga.step = h->steps;
-                gb.step = h->steps + 1;
-                HIP_TRY(h, hipEventRecord(h->fork, h->stream));
-                HIP_TRY(h, hipStreamWaitEvent(h->aux, h->fork, 0));
-                HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2_list(fp2, flist2, nf2, h->stream)));
-                HIP_TRY(h, LBM_DISPATCH(h->prec, general_step<PR>(ga, h->ws + h->L.scratch, h->aux)));
-                HIP_TRY(h, LBM_DISPATCH(h->prec, general_step<PR>(gb, h->ws + h->L.scratch, h->aux)));
-                HIP_TRY(h, hipEventRecord(h->join, h->aux));
-                HIP_TRY(h, hipStreamWaitEvent(h->stream, h->join, 0));
-                h->cur ^= 1;
-                h->steps += 2;
-            }
-        }
-        for (; k < nsteps; ++k) {
-            gp.f_in = fp.f_in = h->fptr(h->cur);
-            gp.u_in = fp.u_in = h->uptr(h->cur);
-            gp.j_in = fp.j_in = h->jptr(h->cur);
-            gp.f_out = fp.f_out = h->fptr(h->cur ^ 1);
-            gp.u_out = fp.u_out = h->uptr(h->cur ^ 1);
-            gp.j_out = fp.j_out = h->jptr(h->cur ^ 1);
-            gp.step = fp.step = h->steps;
-            if (nf > 0) {
-                HIP_TRY(h, hipEventRecord(h->fork, h->stream));
-                HIP_TRY(h, hipStreamWaitEvent(h->aux, h->fork, 0));
-                HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step_list(fp, flist, nf, pc, h->stream)));
-                HIP_TRY(h, LBM_DISPATCH(h->prec, general_step<PR>(gp, h->ws + h->L.scratch, h->aux)));
-                HIP_TRY(h, hipEventRecord(h->join, h->aux));
-                HIP_TRY(h, hipStreamWaitEvent(h->stream, h->join, 0));
-            } else {
-                HIP_TRY(h, LBM_DISPATCH(h->prec, general_step<PR>(gp, h->ws + h->L.scratch, h->stream)));
-            }
-            h->cur ^= 1;
-            h->steps += 1;
-        }
-        return LBM_OK;
     }
-    int64_t k = 0;
     const bool pairs = !h->fused_set && nsteps >= 2 && plan_pairs(h);
     if (h->spl == 2 || pairs) {
         StepParams sp2 = sp;
@@ -1075,29 +872,15 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         sp2.n_segs = shape.n_segs;
         const int nb2 = shape.n_strips * shape.n_segs;
         for (; k + 2 <= nsteps; k += 2) {
-            sp2.f_in = h->fptr(h->cur);
-            sp2.u_in = h->uptr(h->cur);
-            sp2.j_in = h->jptr(h->cur);
-            sp2.f_out = h->fptr(h->cur ^ 1);
-            sp2.u_out = h->uptr(h->cur ^ 1);
-            sp2.j_out = h->jptr(h->cur ^ 1);
-            sp2.step = h->steps;
+            advance(sp2);
             HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2(sp2, shape.block, nb2, h->stream)));
-            h->cur ^= 1;
-            h->steps += 2;
+            done(2);
         }
     }
     for (; k < nsteps; ++k) {
-        sp.f_in = h->fptr(h->cur);
-        sp.u_in = h->uptr(h->cur);
-        sp.j_in = h->jptr(h->cur);
-        sp.f_out = h->fptr(h->cur ^ 1);
-        sp.u_out = h->uptr(h->cur ^ 1);
-        sp.j_out = h->jptr(h->cur ^ 1);
-        sp.step = h->steps;
+        advance(sp);
         HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step(sp, h->shape.block, nblocks, pc, h->stream)));
-        h->cur ^= 1;
-        h->steps += 1;
+        done(1);
     }
     return LBM_OK;
 }

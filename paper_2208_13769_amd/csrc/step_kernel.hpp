@@ -74,7 +74,9 @@ struct StepParams {
     double f_scale, f_inv_scale;  // 16-bit population scaling (1 otherwise)
     int strip_w, n_strips, n_segs;
     int halo_a;             // threads left of the first output column (>= the stencil halo)
-    int x_lo, x_end;        // strips cover columns [x_lo, x_end) (x_end 0: the plate's width)
+    // strips cover columns [x_lo, x_end) and segments rows [y_lo, y_end)
+    // (x_end, y_end 0: the plate's width and height)
+    int x_lo, x_end, y_lo, y_end;
     unsigned int *flag;     // set to 1 on J <= 0 or a non-finite value
     long long step;         // index n of the input state
     int sr;                 // 16-bit populations: 1 = stochastic rounding, 0 = to nearest
@@ -779,8 +781,22 @@ __device__ __forceinline__ TileGeom tile_geom(const StepParams &p, int strip, in
     g.gx = xc % p.nx;
     if (g.gx < 0) g.gx += p.nx;
     g.out_col = (t >= p.halo_a) && (t < p.halo_a + p.strip_w) && (xc < (p.x_end > 0 ? p.x_end : p.nx));
-    g.y0 = (int)((long long)seg * p.ny / p.n_segs);
-    g.y1 = (int)((long long)(seg + 1) * p.ny / p.n_segs);
+    const int rows = (p.y_end > 0 ? p.y_end : p.ny) - p.y_lo;
+    g.y0 = p.y_lo + (int)((long long)seg * rows / p.n_segs);
+    g.y1 = p.y_lo + (int)((long long)(seg + 1) * rows / p.n_segs);
+    return g;
+}
+
+// the tile of a list entry: output columns [e.x, e.x + e.y), rows [e.z, e.w)
+__device__ __forceinline__ TileGeom tile_geom(const StepParams &p, const int4 e)
+{
+    TileGeom g;
+    const int t = threadIdx.x;
+    g.gx = (e.x - p.halo_a + t) % p.nx;
+    if (g.gx < 0) g.gx += p.nx;
+    g.out_col = (t >= p.halo_a) && (t < p.halo_a + e.y);
+    g.y0 = e.z;
+    g.y1 = e.w;
     return g;
 }
 
@@ -813,15 +829,13 @@ using TileLds = typename Pipe<PR, BLOCK, PC, WALLED>::Lds;
 template <int V>
 using Phase = std::integral_constant<int, V>;
 
-// One tile (column strip `strip`, row segment `seg`) of one plate for one
-// time step. Called by every thread of a block; ends with a barrier. The row
+// One tile of one plate for one time step. Called by every thread of a block; ends with a barrier. The row
 // loop is unrolled by four so the register rings rotate by renaming; the row
 // count is rounded up to a multiple of four, and the extra rows lie past the
 // segment's last output row, where nothing is stored or checked.
 template <class PR, int BLOCK, bool PC, bool WALLED>
-__device__ __forceinline__ void step_tile(const StepParams &p, const int strip, const int seg,
-                                          TileLds<PR, BLOCK, PC, WALLED> &lds, const int yr0 = -1,
-                                          const int yr1 = 0)
+__device__ __forceinline__ void step_tile(const StepParams &p, const TileGeom &g,
+                                          TileLds<PR, BLOCK, PC, WALLED> &lds)
 {
     using TF = typename PR::TF;
     using TU = typename PR::TU;
@@ -840,11 +854,6 @@ __device__ __forceinline__ void step_tile(const StepParams &p, const int strip, 
     const int nx = p.nx, ny = p.ny;
     const size_t plane = (size_t)p.plane;
     const TC f_scale = TC(p.f_scale), f_inv = TC(p.f_inv_scale);
-    TileGeom g = tile_geom(p, strip, seg);
-    if (yr0 >= 0) {  // an explicit row range in place of segment seg
-        g.y0 = yr0;
-        g.y1 = yr1;
-    }
     P pipe(lds, p, p.step, (int)threadIdx.x, g.y0, g.y1, g.out_col);
     const bool sr = FS::kStochastic && p.sr;
     const uint32_t key = sr ? sr_key(p.seed, p.step + 1) : 0u;
@@ -1009,10 +1018,9 @@ constexpr int step2_unroll()
 }
 
 template <class PR, int BLOCK, bool WALLED>
-__device__ __forceinline__ void step2_tile(const StepParams &p, const int strip, const int seg,
+__device__ __forceinline__ void step2_tile(const StepParams &p, const TileGeom &g,
                                            TileLds<PR, BLOCK, true, WALLED> &lds1,
-                                           TileLds<PR, BLOCK, true, WALLED> &lds2, const int yr0 = -1,
-                                           const int yr1 = 0)
+                                           TileLds<PR, BLOCK, true, WALLED> &lds2)
 {
     using TF = typename PR::TF;
     using TU = typename PR::TU;
@@ -1031,11 +1039,6 @@ __device__ __forceinline__ void step2_tile(const StepParams &p, const int strip,
     const int nx = p.nx, ny = p.ny;
     const size_t plane = (size_t)p.plane;
     const TC f_scale = TC(p.f_scale), f_inv = TC(p.f_inv_scale);
-    TileGeom g = tile_geom(p, strip, seg);
-    if (yr0 >= 0) {  // an explicit row range in place of segment seg
-        g.y0 = yr0;
-        g.y1 = yr1;
-    }
     P p1(lds1, p, p.step, (int)threadIdx.x, g.y0, g.y1, g.out_col);
     P p2(lds2, p, p.step + 1, (int)threadIdx.x, g.y0, g.y1, g.out_col);
     const bool sr = FS::kStochastic && p.sr;
@@ -1136,37 +1139,33 @@ __global__ void __launch_bounds__(BLOCK) step_kernel(const StepParams p)
     const int seg = logical / p.n_strips;
     const int strip = logical - seg * p.n_strips;
     __shared__ TileLds<PR, BLOCK, PC, WALLED> lds;
-    step_tile<PR, BLOCK, PC, WALLED>(p, strip, seg, lds);
+    step_tile<PR, BLOCK, PC, WALLED>(p, tile_geom(p, strip, seg), lds);
 }
 
-// One step over a list of tiles (strip, first row, end row), three ints per
-// entry: the parts of a plate with x walls or holes that lie clear of them,
-// next to the general step's 2D tiles for the rest. Blocks map to entries
-// as in step_kernel.
-template <class PR, int BLOCK, bool PC, bool WALLED>
-__global__ void __launch_bounds__(BLOCK) step_list_kernel(const StepParams p, const int *__restrict__ list, const int n)
+// One step over a list of tiles: the parts of a plate with x walls or holes
+// that lie clear of them, next to the windows that run the rest, in the
+// periodic form. Blocks map to entries as in step_kernel.
+template <class PR, int BLOCK, bool PC>
+__global__ void __launch_bounds__(BLOCK) step_list_kernel(const StepParams p, const int4 *__restrict__ list, const int n)
 {
     const int bid = blockIdx.x;
     const int xq = n >> 3, xr = n & 7;
     const int xcd = bid & 7, loc = bid >> 3;
     const int logical = xcd * xq + min(xcd, xr) + loc;
-    const int *e = list + 3 * logical;
-    __shared__ TileLds<PR, BLOCK, PC, WALLED> lds;
-    step_tile<PR, BLOCK, PC, WALLED>(p, e[0], 0, lds, e[1], e[2]);
+    __shared__ TileLds<PR, BLOCK, PC, false> lds;
+    step_tile<PR, BLOCK, PC, false>(p, tile_geom(p, list[logical]), lds);
 }
 
-// Two steps over a tile list (strip, first row, end row), as step_list_kernel.
-template <class PR, int BLOCK, bool WALLED>
-__global__ void __launch_bounds__(BLOCK) step2_list_kernel(const StepParams p, const int *__restrict__ list,
-                                                           const int n)
+// Two steps over a tile list, as step_list_kernel.
+template <class PR, int BLOCK>
+__global__ void __launch_bounds__(BLOCK) step2_list_kernel(const StepParams p, const int4 *__restrict__ list, const int n)
 {
     const int bid = blockIdx.x;
     const int xq = n >> 3, xr = n & 7;
     const int xcd = bid & 7, loc = bid >> 3;
     const int logical = xcd * xq + min(xcd, xr) + loc;
-    const int *e = list + 3 * logical;
-    __shared__ TileLds<PR, BLOCK, true, WALLED> lds[2];
-    step2_tile<PR, BLOCK, WALLED>(p, e[0], 0, lds[0], lds[1], e[1], e[2]);
+    __shared__ TileLds<PR, BLOCK, true, false> lds[2];
+    step2_tile<PR, BLOCK, false>(p, tile_geom(p, list[logical]), lds[0], lds[1]);
 }
 
 // Two steps per launch, one block per tile (same tile order as step_kernel).
@@ -1181,7 +1180,7 @@ __global__ void __launch_bounds__(BLOCK) step2_kernel(const StepParams p)
     const int seg = logical / p.n_strips;
     const int strip = logical - seg * p.n_strips;
     __shared__ TileLds<PR, BLOCK, true, WALLED> lds[2];
-    step2_tile<PR, BLOCK, WALLED>(p, strip, seg, lds[0], lds[1]);
+    step2_tile<PR, BLOCK, WALLED>(p, tile_geom(p, strip, seg), lds[0], lds[1]);
 }
 
 }  // namespace lbm

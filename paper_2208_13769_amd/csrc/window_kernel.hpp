@@ -27,25 +27,73 @@
 // times that); on larger ones the issue of those instructions, with the rings
 // computed twice. Per step against the fused kernel's plan, which marches 12
 // or more dependent rows: 64^2 FP64 4.2 us (12.3), 256^2 FP32_U64 5.1 (16.4),
-// 512^2 FP32_U64 9.5 (19.5), between y walls 11.3 (23.7); 80^2 FP64 with a
-// hole 8.2 (17.0 with the 2D tiles, which spent 1500 of 2500 vector
-// instructions on index arithmetic).
+// 512^2 FP32_U64 9.5 (19.5), between y walls 10.9 (23.6); 100 x 150 with a hole
+// FP64 8.3 (29.1 with the 2D tiles these replace, which spent 1500 of 2500
+// vector instructions on index arithmetic, beside a fused share).
 #pragma once
 
 #include <algorithm>
 #include <cmath>
+#include <vector>
 
 #include "../../include/lbm_solid.h"
-#include "general_kernels.hpp"
+#include "step_kernel.hpp"
 
 namespace lbm {
 
+enum : int { EDGE_XMIN = 0, EDGE_XMAX = 1, EDGE_YMIN = 2, EDGE_YMAX = 3 };
+
+// Plate, state and edges of a window launch.
+struct GenParams {
+    const void *f_in, *u_in, *j_in;  // state n
+    void *f_out, *u_out, *j_out;     // state n + 1
+    const void *j_prev;              // j_{n-1} (j-extrapolation only)
+    int nx, ny;
+    long long plane;
+    double omega, lam, mu, bx, by;  // lattice units
+    int bc[4];                      // rule of each edge (BC_*), EDGE_* order
+    double val[4][2];               // j* or T* of each edge, lattice units
+    double uwb[4][2];               // momentum walls: displacement uwb + j* n at step n
+    double f_scale, f_inv_scale;
+    long long step;                 // index n of the input state
+    int sr;
+    unsigned long long seed;
+    int pc;  // explicit (0), predictor-corrector (1), j extrapolated for the predictor (2)
+    unsigned *flag;
+    const unsigned char *mask;  // [ny][nx]: 1 material, 0 hole; nullptr: no holes
+};
+
+// D2Q9 of this implementation (see lattice.hpp)
+__device__ constexpr int kGx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
+__device__ constexpr int kGy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
+__device__ constexpr int kGopp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
+
+// Ghost value k = 1 or 2 spacings beyond a wall from the node next to it
+// (a): at a momentum wall the straight line through the wall displacement
+// uw and a (2 uw - a, then 4 uw - 3 a), at a traction wall the value a.
+template <class TU>
+__device__ __forceinline__ TU gen_ghost(int kind, TU uw, TU a, int k)
+{
+    if (kind == BC_NEUMANN) return a;
+    return k == 1 ? TU(2) * uw - a : TU(4) * uw - TU(3) * a;
+}
+
 constexpr int kWinMaxSteps = 2;  // steps per launch at most
 
-// Geometry of a launch: output rectangle of a block, blocks per row, blocks,
-// steps; the momentum walls' displacement at steps n .. n + nsteps.
+// A rectangle of a plate tiled with windows: out_w x out_h nodes per block,
+// nbx blocks per row of blocks, the first one block `first` of the launch.
+struct WinRegion {
+    int x, y, w, h, out_w, out_h, nbx, first;
+};
+constexpr int kWinRegions = 4;  // regions of a launch without a list: a frame's bands
+
+// Geometry of a launch: blocks, steps, the output rectangles (a list in device
+// memory, x, y, w, h per block, or regions); the momentum walls' displacement
+// at steps n .. n + nsteps.
 struct WinGrid {
-    int out_w, out_h, nbx, nb, nsteps;
+    int nb, nsteps, n_regions;
+    WinRegion reg[kWinRegions];
+    const int4 *list;
     double uw[kWinMaxSteps + 1][4][2];
 };
 
@@ -80,12 +128,19 @@ struct Window {
     static constexpr bool DEV = FS::kDeviation;
     static constexpr int N = WW * WH, BLOCK = N / K, RS = BLOCK / WW;  // RS: rows between a thread's sites
     static constexpr int HS = win_reach<MODE>();
+    static constexpr int CAP = N / 4;  // wall nodes handled at once
+    static_assert(N <= 2048, "LDS index in 11 bits");
     static_assert((WW & (WW - 1)) == 0 && BLOCK % WW == 0 && RS * K == WH, "window shape");
     struct Lds {
         TU u[2][N];
         TC k[4][N];
         TC f[8][N];  // directions 1..8
         unsigned char hole[GEN == WIN_GENERAL ? N : 1];
+        // WIN_GENERAL: nodes beside a wall or hole (LDS index, flags << 11; 0:
+        // none), the moments of their populations, and how many there are
+        unsigned wn[GEN == WIN_GENERAL ? CAP : 1];
+        TC wm[GEN == WIN_GENERAL ? 4 : 1][GEN == WIN_GENERAL ? CAP : 1];
+        int nw;
     };
 
     // bits of a site's flags
@@ -186,9 +241,7 @@ struct Window {
     // K at the hole neighbour across axis n as a node with gradient H sees it
     __device__ __forceinline__ void k_hole(const TC H[4], int n, TC Kh[4]) const
     {
-        TC Hn[4] = {H[0], H[1], H[2], H[3]};
-        Hn[n] = TC(0);
-        Hn[2 + n] = TC(0);
+        const TC Hn[4] = {n ? H[0] : TC(0), n ? TC(0) : H[1], n ? H[2] : TC(0), n ? TC(0) : H[3]};
         stress_sum(Hn, lam, mu, Kh);
     }
 
@@ -216,141 +269,96 @@ struct Window {
     // slot of the value pulled in direction d at site i
     __device__ __forceinline__ static int slot(int i, int d) { return i - kGy[d] * WW - kGx[d]; }
 
-    // Whether the diagonal link (ox, oy) of a node crosses walls, and which:
-    // bit 0 the x side's, bit 1 the y side's. A link into a hole crosses the
-    // wall its axis step enters, or both through a hole corner.
-    __device__ __forceinline__ static int crossed(unsigned fl, int o, int ox, int oy)
+    // y walls: the values the wall returns to its node i, into the slots the
+    // pull reads, in the fused kernel's form. m: r, Pxx of the node's
+    // populations, whose values after the collision are in the LDS.
+    __device__ __forceinline__ void wall_row(int i, unsigned fl, TC r, TC pxx)
     {
-        const bool hole = near(fl, o);
-        const bool hx = near(fl, ox > 0 ? 1 : 3), hy = near(fl, oy > 0 ? 2 : 4);
-        const bool bx = hole ? (hx || !hy) : (fl & (ox < 0 ? XL : XH)) != 0;
-        const bool by = hole ? (hy || !hx) : (fl & (oy < 0 ? YL : YH)) != 0;
-        return (bx ? 1 : 0) | (by ? 2 : 0);
+        const bool top = opaque(fl) & YH;
+        const int g = top ? i + WW : i - WW;
+        const double val[2] = {top ? p.val[EDGE_YMAX][0] : p.val[EDGE_YMIN][0],
+                               top ? p.val[EDGE_YMAX][1] : p.val[EDGE_YMIN][1]};
+        const TC fco[3] = {L.f[top ? 1 : 3][i], L.f[top ? 4 : 6][i], L.f[top ? 5 : 7][i]};
+        TC w[3];
+        wall_populations(top, top ? p.bc[EDGE_YMAX] : p.bc[EDGE_YMIN], fco, val, r, pxx,
+                         TC(0.5) * (L.k[1][i] + L.k[1][g]), TC(0.5) * (L.k[3][i] + L.k[3][g]), w);
+        // returned as 4, 7, 8 (top) or 2, 5, 6
+        L.f[top ? 3 : 1][g] = w[0];
+        L.f[top ? 6 : 4][top ? g + 1 : g - 1] = w[1];
+        L.f[top ? 7 : 5][top ? g - 1 : g + 1] = w[2];
     }
 
-    // One wall of WIN_GENERAL on side S (-1: low, 1: high) of axis A of node i:
-    // the values it returns for the axis link and for the two diagonals that
-    // cross this wall alone, into the slots the pull reads. m: r, Pxx, Pyy,
-    // Pxy of the node's populations, whose values after the collision are in
-    // the LDS. eq. (25), (26) with r_bd and the tangential moments at the
-    // node; K at the wall is the mean of the node's and the one beyond it (a
-    // ghost node, or at a hole, T* = 0, the hole K the node sees).
-    template <int A, int S>
-    __device__ __forceinline__ void side(int i, unsigned fl, const TC H[4], const TC m[4])
+    // Value returned for the link o of node i if it leaves through a wall or
+    // into a hole, into the slot the pull reads (m: r, Pxx, Pyy, Pxy of the
+    // node's populations, whose values after the collision are in the LDS).
+    // Bounce-back with the wall momentum (eq. (25)) if a crossed wall is a
+    // momentum wall (the mean j* if both are); otherwise anti-bounce-back (eq.
+    // (26)) with r_bd and Pbar* at the node: each traction wall's column of
+    // Pbar* is -s T* + K n, K at the wall the mean of the node's and the one
+    // beyond it (a ghost node, or at a hole, T* = 0, the hole K the node
+    // sees); a tangential entry keeps the populations' second moment, and at a
+    // corner the off-diagonal entry is the mean of both walls' values.
+    __device__ __forceinline__ void link(int o, int i, unsigned fl, const TC m[4], const double uw[4][2])
     {
-        constexpr int o0 = A ? (S > 0 ? 2 : 4) : (S > 0 ? 1 : 3);
-        const bool hole = near(fl, o0);
-        if (!hole && !(fl & (A ? (S > 0 ? YH : YL) : (S > 0 ? XH : XL)))) return;
-        constexpr int e = A ? (S > 0 ? EDGE_YMAX : EDGE_YMIN) : (S > 0 ? EDGE_XMAX : EDGE_XMIN);
-        constexpr int o1 = A ? (S > 0 ? 5 : 8) : (S > 0 ? 5 : 6);  // diagonals: e_t = 1, then -1 along the wall
-        constexpr int o2 = A ? (S > 0 ? 6 : 7) : (S > 0 ? 8 : 7);
-        const TC f0 = L.f[o0 - 1][i], f1 = L.f[o1 - 1][i], f2 = L.f[o2 - 1][i];
-        const TC s = TC(S), w1 = TC(1.0 / 9.0), w5 = TC(1.0 / 36.0);
-        const double t0 = hole ? 0.0 : p.val[e][0], t1 = hole ? 0.0 : p.val[e][1];
-        TC v0, v1, v2;
-        if (!hole && p.bc[e] == BC_DIRICHLET) {
-            const TC jn = TC(A ? t1 : t0), jt = TC(A ? t0 : t1);
-            v0 = f0 - TC(6) * w1 * (s * jn);
-            v1 = f1 - TC(6) * w5 * (s * jn + jt);
-            v2 = f2 - TC(6) * w5 * (s * jn - jt);
+        const int ox = (int)((0x20919u >> (2 * o)) & 3u) - 1, oy = (int)((0x2865u >> (2 * o)) & 3u) - 1;
+        const bool hole = near(fl, o);
+        const bool bx = ox != 0 && (fl & (ox < 0 ? XL : XH)), by = oy != 0 && (fl & (oy < 0 ? YL : YH));
+        if (!(hole || bx || by)) return;
+        // holes beside the node across x and y; a link into a hole crosses the
+        // wall its axis step enters, or both through a hole corner
+        const bool nx = ox != 0 && near(fl, ox > 0 ? 1 : 3), ny = oy != 0 && near(fl, oy > 0 ? 2 : 4);
+        const int sx = (hole ? nx || !ny : bx) ? ox : 0, sy = (hole ? ny || !nx : by) ? oy : 0;
+        const bool lx = ox < 0, ly = oy < 0;
+        const bool ddx = !hole && sx != 0 && (lx ? p.bc[EDGE_XMIN] : p.bc[EDGE_XMAX]) == BC_DIRICHLET;
+        const bool ddy = !hole && sy != 0 && (ly ? p.bc[EDGE_YMIN] : p.bc[EDGE_YMAX]) == BC_DIRICHLET;
+        // j* or T* of the edges (selected from scalars: an index would load)
+        const double vx0 = lx ? p.val[EDGE_XMIN][0] : p.val[EDGE_XMAX][0];
+        const double vx1 = lx ? p.val[EDGE_XMIN][1] : p.val[EDGE_XMAX][1];
+        const double vy0 = ly ? p.val[EDGE_YMIN][0] : p.val[EDGE_YMAX][0];
+        const double vy1 = ly ? p.val[EDGE_YMIN][1] : p.val[EDGE_YMAX][1];
+        const TC w = o < 5 ? TC(1.0 / 9.0) : TC(1.0 / 36.0), cx = TC(ox), cy = TC(oy), fco = L.f[o - 1][i];
+        TC val;
+        if (ddx || ddy) {
+            const double sc = ddx && ddy ? 0.5 : 1.0;
+            const TC jx = TC(sc * ((ddx ? vx0 : 0.0) + (ddy ? vy0 : 0.0)));
+            const TC jy = TC(sc * ((ddx ? vx1 : 0.0) + (ddy ? vy1 : 0.0)));
+            val = fco - TC(6) * w * (cx * jx + cy * jy);
         } else {
-            const int g = A ? i + S * WW : i + S;
-            TC ka = L.k[A][g], kb = L.k[2 + A][g];
-            if (hole) {
-                TC kh[4];
-                k_hole(H, A, kh);
-                ka = kh[A];
-                kb = kh[2 + A];
+            TC H[4] = {TC(0), TC(0), TC(0), TC(0)}, kh[4];
+            if (fl >> 8) grad(i, fl, uw, H);
+            TC Pxx = m[1], Pyy = m[2], Pxy = m[3], qx1 = TC(0);
+            if (sx) {
+                TC k0 = L.k[0][i + sx], k2 = L.k[2][i + sx];
+                if (nx) {
+                    k_hole(H, 0, kh);
+                    k0 = kh[0];
+                    k2 = kh[2];
+                }
+                Pxx = -cx * TC(hole ? 0.0 : vx0) + TC(0.5) * (L.k[0][i] + k0);
+                Pxy = qx1 = -cx * TC(hole ? 0.0 : vx1) + TC(0.5) * (L.k[2][i] + k2);
             }
-            // the wall's column of Pbar*
-            const TC q0 = -s * TC(t0) + TC(0.5) * (L.k[A][i] + ka), q1 = -s * TC(t1) + TC(0.5) * (L.k[2 + A][i] + kb);
-            const TC Pxx = A ? m[1] : q0, Pyy = A ? q1 : m[2], Pxy = A ? q0 : q1;
+            if (sy) {
+                TC k1 = L.k[1][i + sy * WW], k3 = L.k[3][i + sy * WW];
+                if (ny) {
+                    k_hole(H, 1, kh);
+                    k1 = kh[1];
+                    k3 = kh[3];
+                }
+                const TC qy0 = -cy * TC(hole ? 0.0 : vy0) + TC(0.5) * (L.k[1][i] + k1);
+                Pyy = -cy * TC(hole ? 0.0 : vy1) + TC(0.5) * (L.k[3][i] + k3);
+                Pxy = sx ? TC(0.5) * (qx1 + qy0) : qy0;
+            }
             const TC r = m[0], third = TC(1) / TC(3);
             const TC axx = Pxx - r * third, ayy = Pyy - r * third;
-            const TC tr = axx + ayy, an = A ? ayy : axx;
-            const TC d1 = (axx + TC(2) * (s * Pxy)) + ayy, d2 = (axx - TC(2) * (s * Pxy)) + ayy;
-            v0 = -f0 + TC(2) * w1 * (r + TC(4.5) * (an - tr * third));
-            v1 = -f1 + TC(2) * w5 * (r + TC(4.5) * (d1 - tr * third));
-            v2 = -f2 + TC(2) * w5 * (r + TC(4.5) * (d2 - tr * third));
+            const TC q = axx * cx * cx + TC(2) * Pxy * cx * cy + ayy * cy * cy - (axx + ayy) * third;
+            val = -fco + TC(2) * w * (r + TC(4.5) * q);
         }
-        constexpr int only = A ? 2 : 1;
-        L.f[kGopp[o0] - 1][i + kGy[o0] * WW + kGx[o0]] = v0;
-        if (crossed(fl, o1, kGx[o1], kGy[o1]) == only) L.f[kGopp[o1] - 1][i + kGy[o1] * WW + kGx[o1]] = v1;
-        if (crossed(fl, o2, kGx[o2], kGy[o2]) == only) L.f[kGopp[o2] - 1][i + kGy[o2] * WW + kGx[o2]] = v2;
+        // the opposite link's plane (d - 1), at the site this one leads to
+        L.f[(0x54761032u >> (4 * (o - 1))) & 7u][i + oy * WW + ox] = val;
     }
 
-    // Values the walls return to node i, into the slots its pull reads (m, H:
-    // as side). y walls alone take the fused kernel's form. The general form
-    // goes one side at a time, three links each, then over the diagonals that
-    // cross two walls: the off-diagonal entry of Pbar* is the mean of both
-    // walls' values, a momentum wall (the mean j* of two) bounces back. (A
-    // rolled loop over eight links with the two-wall rule for each: 8.8 us per
-    // step on the 64 x 64 plate with a hole in FP64 with 16 x 16 windows,
-    // against 8.2.)
-    __device__ __forceinline__ void walls(int i, unsigned fl, const TC H[4], const TC m[4])
-    {
-        fl = opaque(fl);
-        if constexpr (GEN == WIN_YWALLS) {
-            const bool top = fl & YH;
-            const int g = top ? i + WW : i - WW;
-            const double val[2] = {top ? p.val[EDGE_YMAX][0] : p.val[EDGE_YMIN][0],
-                                   top ? p.val[EDGE_YMAX][1] : p.val[EDGE_YMIN][1]};
-            const TC fco[3] = {L.f[top ? 1 : 3][i], L.f[top ? 4 : 6][i], L.f[top ? 5 : 7][i]};
-            TC w[3];
-            wall_populations(top, top ? p.bc[EDGE_YMAX] : p.bc[EDGE_YMIN], fco, val, m[0], m[1],
-                             TC(0.5) * (L.k[1][i] + L.k[1][g]), TC(0.5) * (L.k[3][i] + L.k[3][g]), w);
-            // returned as 4, 7, 8 (top) or 2, 5, 6
-            L.f[top ? 3 : 1][g] = w[0];
-            L.f[top ? 6 : 4][top ? g + 1 : g - 1] = w[1];
-            L.f[top ? 7 : 5][top ? g - 1 : g + 1] = w[2];
-            return;
-        }
-        side<0, -1>(i, fl, H, m);
-        side<0, 1>(i, fl, H, m);
-        side<1, -1>(i, fl, H, m);
-        side<1, 1>(i, fl, H, m);
-#pragma unroll 1
-        for (int o = 5; o < 9; ++o) {
-            const int ox = o == 5 || o == 8 ? 1 : -1, oy = o < 7 ? 1 : -1;
-            if (crossed(fl, o, ox, oy) != 3) continue;
-            const bool hole = near(fl, o);
-            const int ex = ox < 0 ? EDGE_XMIN : EDGE_XMAX, ey = oy < 0 ? EDGE_YMIN : EDGE_YMAX;
-            const bool ddx = !hole && p.bc[ex] == BC_DIRICHLET, ddy = !hole && p.bc[ey] == BC_DIRICHLET;
-            const TC w = TC(1.0 / 36.0), cx = TC(ox), cy = TC(oy), fco = L.f[o - 1][i];
-            TC val;
-            if (ddx || ddy) {
-                const double sc = ddx && ddy ? 0.5 : 1.0;
-                const TC jx = TC(sc * ((ddx ? p.val[ex][0] : 0.0) + (ddy ? p.val[ey][0] : 0.0)));
-                const TC jy = TC(sc * ((ddx ? p.val[ex][1] : 0.0) + (ddy ? p.val[ey][1] : 0.0)));
-                val = fco - TC(6) * w * (cx * jx + cy * jy);
-            } else {
-                TC kx0 = L.k[0][i + ox], kx2 = L.k[2][i + ox], ky1 = L.k[1][i + oy * WW], ky3 = L.k[3][i + oy * WW];
-                TC kh[4];
-                if (near(fl, ox > 0 ? 1 : 3)) {
-                    k_hole(H, 0, kh);
-                    kx0 = kh[0];
-                    kx2 = kh[2];
-                }
-                if (near(fl, oy > 0 ? 2 : 4)) {
-                    k_hole(H, 1, kh);
-                    ky1 = kh[1];
-                    ky3 = kh[3];
-                }
-                const TC Pxx = -cx * TC(hole ? 0.0 : p.val[ex][0]) + TC(0.5) * (L.k[0][i] + kx0);
-                const TC qx1 = -cx * TC(hole ? 0.0 : p.val[ex][1]) + TC(0.5) * (L.k[2][i] + kx2);
-                const TC qy0 = -cy * TC(hole ? 0.0 : p.val[ey][0]) + TC(0.5) * (L.k[1][i] + ky1);
-                const TC Pyy = -cy * TC(hole ? 0.0 : p.val[ey][1]) + TC(0.5) * (L.k[3][i] + ky3);
-                const TC Pxy = TC(0.5) * (qx1 + qy0);
-                const TC third = TC(1) / TC(3);
-                const TC axx = Pxx - m[0] * third, ayy = Pyy - m[0] * third;
-                const TC d = (axx + TC(2) * (cx * cy * Pxy)) + ayy;
-                val = -fco + TC(2) * w * (m[0] + TC(4.5) * (d - (axx + ayy) * third));
-            }
-            L.f[o < 7 ? o + 1 : o - 3][i + oy * WW + ox] = val;
-        }
-    }
-
-    __device__ __forceinline__ void run(const WinGrid &g, int x0, int y0)
+    // the output rectangle: ow x oh nodes from (x0, y0)
+    __device__ __forceinline__ void run(const WinGrid &g, int x0, int y0, int ow, int oh)
     {
         const size_t pl = (size_t)p.plane;
         const TF *__restrict__ fin = static_cast<const TF *>(p.f_in);
@@ -358,7 +366,6 @@ struct Window {
         const TJ *__restrict__ jin = static_cast<const TJ *>(p.j_in);
         const int nx = p.nx, ny = p.ny;
         const int h = g.nsteps * HS + (DEV ? 1 : 0);
-        const int ow = min(g.out_w, nx - x0), oh = min(g.out_h, ny - y0);
         const int rows = oh + 2 * h, cols = ow + 2 * h;  // of the window that are used
         const bool perx = p.bc[EDGE_XMIN] == BC_PERIODIC, pery = p.bc[EDGE_YMIN] == BC_PERIODIC;
         const TC omega = TC(p.omega), inv = TC(p.f_inv_scale), scale = TC(p.f_scale);
@@ -372,6 +379,7 @@ struct Window {
         uint32_t site[K];
         unsigned fl[K];
         bool out[K];
+        int pos[K];  // WIN_GENERAL: place in the list of wall nodes
         auto row_in = [&](int k, int d) { return r0 + k * RS >= d && r0 + k * RS < rows - d; };
 
         const int ux = x0 - h + lx;
@@ -447,6 +455,16 @@ struct Window {
                 }
             }
         }
+        int nw = 0;
+        if constexpr (GEN == WIN_GENERAL) {
+            if (threadIdx.x == 0) L.nw = 0;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                pos[k] = -1;
+                if ((fl[k] & NODE) && ((fl[k] & EDGE) || (fl[k] >> 8))) pos[k] = atomicAdd(&L.nw, 1);
+            }
+        }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
 #pragma unroll
@@ -460,6 +478,7 @@ struct Window {
             const double(*uw)[2] = g.uw[s], (*uw1)[2] = g.uw[s + 1];
             TC H[K][4], S[K][2];
             __syncthreads();
+            if (GEN == WIN_GENERAL && s == 0) nw = L.nw;
             // K of u_n; with deviation storage the populations from the
             // stored deviations (a further step takes them as a store and
             // load would leave them)
@@ -489,6 +508,7 @@ struct Window {
             }
             __syncthreads();
             // source and collision
+            TC m[K][4];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 if (!row_in(k, d + 2)) continue;
@@ -499,13 +519,40 @@ struct Window {
                 collide(f[k], j[k][0], j[k][1], S[k][0], S[k][1], omega, fc, r, pxx);
 #pragma unroll
                 for (int q = 1; q < 9; ++q) L.f[q - 1][i] = fc[q];
-                if (GEN && (fl[k] & (EDGE | ~(NEAR * 2u - 1u)))) {
+                if (GEN == WIN_GENERAL || (GEN == WIN_YWALLS && (fl[k] & EDGE))) {
                     const TC *fk = f[k];
-                    const TC m[4] = {r, pxx, (fk[2] + fk[4]) + ((fk[5] + fk[6]) + (fk[7] + fk[8])),
-                                     (fk[5] - fk[6]) + (fk[7] - fk[8])};
-                    walls(i, fl[k], H[k], m);
+                    m[k][0] = r;
+                    m[k][1] = pxx;
+                    m[k][2] = (fk[2] + fk[4]) + ((fk[5] + fk[6]) + (fk[7] + fk[8]));
+                    m[k][3] = (fk[5] - fk[6]) + (fk[7] - fk[8]);
+                    if constexpr (GEN == WIN_YWALLS) wall_row(i, fl[k], r, pxx);
                 }
                 f[k][0] = fc[0];
+            }
+            if constexpr (GEN == WIN_GENERAL) {
+                // The links of the nodes beside walls and holes, one per
+                // thread: an x wall puts one such node in every row of the
+                // window, and run where it lies each wave would go through all
+                // its links for one lane (the windows of the 4096^2 FP32_U64
+                // plate with a hole: 113 against 147 us per two steps).
+                for (int base = 0; base < nw; base += CAP) {
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const int q = pos[k] - base;
+                        if (pos[k] < 0 || q < 0 || q >= CAP) continue;
+                        L.wn[q] = row_in(k, d + 2) ? (unsigned)((r0 + k * RS) * WW + lx) | (fl[k] << 11) : 0u;
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) L.wm[c][q] = m[k][c];
+                    }
+                    __syncthreads();
+                    for (int q = threadIdx.x; q < 8 * min(CAP, nw - base); q += BLOCK) {
+                        const int n = q >> 3;
+                        const unsigned e = L.wn[n];
+                        const TC mq[4] = {L.wm[0][n], L.wm[1][n], L.wm[2][n], L.wm[3][n]};
+                        if (e) link((int)opaque((q & 7) + 1), (int)(e & 2047u), e >> 11, mq, uw);
+                    }
+                    if (base + CAP < nw) __syncthreads();
+                }
             }
             __syncthreads();
             // pull streaming, moments, predictor (or the explicit update)
@@ -608,6 +655,9 @@ struct Window {
     }
 };
 
+// One block per output rectangle. Blocks are dealt round-robin to the 8 XCDs;
+// the remap gives each XCD a run of consecutive rectangles, so the windows of
+// horizontal neighbours overlap in one L2.
 template <class PR, int MODE, int WW, int WH, int K, int GEN>
 __global__ void __launch_bounds__(WW *WH / K) window_step_kernel(const GenParams p, const WinGrid g)
 {
@@ -617,9 +667,23 @@ __global__ void __launch_bounds__(WW *WH / K) window_step_kernel(const GenParams
     const int xq = g.nb >> 3, xr = g.nb & 7;
     const int xcd = bid & 7, loc = bid >> 3;
     const int tile = xcd * xq + min(xcd, xr) + loc;
-    const int ty = tile / g.nbx, tx = tile - ty * g.nbx;
+    int x0, y0, ow, oh;
+    if (g.list) {
+        const int4 e = g.list[tile];
+        x0 = e.x, y0 = e.y, ow = e.z, oh = e.w;
+    } else {
+        int q = 0;
+        for (int k = 1; k < g.n_regions; ++k)
+            if (tile >= g.reg[k].first) q = k;
+        const WinRegion &r = g.reg[q];
+        const int t = tile - r.first, ty = t / r.nbx, tx = t - ty * r.nbx;
+        x0 = r.x + tx * r.out_w;
+        y0 = r.y + ty * r.out_h;
+        ow = min(r.out_w, r.x + r.w - x0);
+        oh = min(r.out_h, r.y + r.h - y0);
+    }
     W w(p, lds);
-    w.run(g, tx * g.out_w, ty * g.out_h);
+    w.run(g, x0, y0, ow, oh);
 }
 
 // Window shapes: columns, rows, rows per thread.
@@ -633,7 +697,7 @@ constexpr int kNumWinShapes = (int)(sizeof(kWinShapes) / sizeof(kWinShapes[0]));
 // at least lat (up to one block per compute unit), base + thr per block on
 // the fullest compute unit beyond. Measured with plates of 16 to 2048 full
 // windows, per class (double; float; float with a double displacement; 16-bit
-// storage) and for periodic plates and plates with walls or holes. A two-step
+// storage) and kind of edges (WIN_*). A two-step
 // launch pays where the plate is small enough that the launch itself and the
 // load of the state count (64 x 64 FP64: 4.2 us per step with two 32 x 32
 // steps, 4.3 with 16 x 16 and 7.0 with 32 x 32 windows of one step).
@@ -641,24 +705,38 @@ struct WinCost {
     int shape, steps;
     float lat, base, thr;
 };
-constexpr int kNumWinCosts = 8;
-constexpr WinCost kWinCosts[4][2][kNumWinCosts] = {
+constexpr int kNumWinCosts = 9;
+constexpr WinCost kWinCosts[4][3][kNumWinCosts] = {
     {{{0, 1, 4.4f, 3.3f, 0.9f}, {1, 1, 5.6f, 2.3f, 2.4f}, {2, 1, 9.0f, 3.3f, 7.2f}, {2, 2, 9.8f, 3.0f, 7.3f},
       {3, 1, 8.4f, 1.6f, 5.8f}, {5, 1, 9.4f, 3.2f, 7.5f}},
-     {{0, 1, 7.2f, 4.9f, 1.4f}, {1, 1, 8.0f, 4.1f, 3.9f}, {2, 1, 12.3f, 5.8f, 8.3f}, {2, 2, 14.7f, 5.9f, 9.5f},
-      {3, 1, 10.3f, 4.6f, 6.9f}, {5, 1, 12.1f, 4.9f, 8.6f}}},
+     {{0, 1, 5.6f, 4.3f, 1.0f}, {1, 1, 6.3f, 2.9f, 2.5f}, {2, 1, 9.8f, 3.6f, 7.4f}, {2, 2, 10.4f, 3.4f, 7.7f},
+      {3, 1, 8.8f, 2.1f, 6.0f}, {5, 1, 10.9f, 4.1f, 8.1f}, {5, 2, 11.8f, 4.3f, 8.5f}},
+     {{0, 1, 6.9f, 4.7f, 1.7f}, {1, 1, 8.2f, 5.0f, 4.2f}, {2, 1, 15.9f, 5.6f, 11.6f}, {2, 2, 19.6f, 7.8f, 13.4f},
+      {3, 1, 14.1f, 7.2f, 9.3f}, {5, 1, 13.7f, 5.7f, 9.1f}, {5, 2, 17.1f, 10.3f, 10.4f}}},
     {{{0, 1, 3.9f, 3.2f, 0.5f}, {1, 1, 4.4f, 3.2f, 1.0f}, {2, 1, 6.1f, 2.2f, 3.2f}, {2, 2, 6.6f, 2.9f, 3.0f},
       {3, 1, 5.6f, 2.1f, 2.4f}, {4, 1, 10.0f, 5.2f, 7.1f}, {4, 2, 11.1f, 2.4f, 7.9f}, {5, 1, 6.8f, 2.4f, 3.3f}},
-     {{0, 1, 6.4f, 5.5f, 0.6f}, {1, 1, 6.7f, 3.8f, 1.8f}, {2, 1, 8.1f, 4.1f, 4.4f}, {2, 2, 10.8f, 5.5f, 5.5f},
-      {3, 1, 7.2f, 3.8f, 3.8f}, {4, 1, 11.8f, 6.7f, 7.9f}, {4, 2, 14.0f, 5.8f, 9.0f}, {5, 1, 9.3f, 4.2f, 3.7f}}},
+     {{0, 1, 5.2f, 4.2f, 0.5f}, {1, 1, 5.3f, 3.4f, 1.3f}, {2, 1, 6.7f, 2.6f, 4.0f}, {2, 2, 7.7f, 2.9f, 4.9f},
+      {3, 1, 6.1f, 2.6f, 2.6f}, {4, 1, 10.9f, 5.4f, 7.6f}, {4, 2, 11.9f, 3.3f, 8.4f}, {5, 1, 7.8f, 3.3f, 3.4f},
+      {5, 2, 9.3f, 2.2f, 4.3f}},
+     {{0, 1, 6.5f, 4.8f, 1.0f}, {1, 1, 6.9f, 3.5f, 2.2f}, {2, 1, 8.8f, 5.1f, 5.1f}, {2, 2, 11.2f, 7.3f, 6.4f},
+      {3, 1, 8.2f, 4.8f, 4.5f}, {4, 1, 13.7f, 5.6f, 9.8f}, {4, 2, 17.4f, 9.8f, 10.5f}, {5, 1, 10.6f, 6.2f, 6.3f},
+      {5, 2, 13.5f, 8.0f, 8.2f}}},
     {{{0, 1, 3.9f, 3.3f, 0.5f}, {1, 1, 4.5f, 3.4f, 1.0f}, {2, 1, 6.6f, 2.6f, 3.4f}, {2, 2, 7.2f, 3.0f, 3.4f},
       {3, 1, 6.1f, 2.0f, 2.8f}, {4, 1, 11.4f, 0.0f, 11.1f}, {4, 2, 12.6f, 2.2f, 9.2f}, {5, 1, 7.2f, 2.7f, 3.7f}},
-     {{0, 1, 6.4f, 5.4f, 0.7f}, {1, 1, 6.8f, 3.9f, 1.8f}, {2, 1, 8.3f, 4.0f, 4.8f}, {2, 2, 10.9f, 5.8f, 5.6f},
-      {3, 1, 7.3f, 3.6f, 4.0f}, {4, 1, 13.7f, 0.0f, 12.6f}, {4, 2, 15.4f, 5.4f, 10.5f}, {5, 1, 9.5f, 4.7f, 5.6f}}},
+     {{0, 1, 5.2f, 4.3f, 0.6f}, {1, 1, 5.4f, 3.4f, 1.4f}, {2, 1, 7.2f, 2.5f, 4.5f}, {2, 2, 8.2f, 2.9f, 5.3f},
+      {3, 1, 6.5f, 2.4f, 3.7f}, {4, 1, 12.1f, 0.6f, 11.3f}, {4, 2, 13.4f, 2.8f, 9.8f}, {5, 1, 8.2f, 3.6f, 3.7f},
+      {5, 2, 9.5f, 2.4f, 4.7f}},
+     {{0, 1, 6.5f, 4.9f, 1.0f}, {1, 1, 7.1f, 3.6f, 2.3f}, {2, 1, 9.3f, 5.2f, 5.4f}, {2, 2, 11.5f, 7.4f, 6.9f},
+      {3, 1, 8.7f, 5.2f, 4.7f}, {4, 1, 15.5f, 2.7f, 12.9f}, {4, 2, 19.3f, 10.9f, 11.5f}, {5, 1, 11.0f, 6.5f, 6.5f},
+      {5, 2, 14.3f, 9.5f, 8.2f}}},
     {{{0, 1, 4.3f, 3.5f, 0.6f}, {1, 1, 4.5f, 2.9f, 1.3f}, {2, 1, 6.3f, 2.3f, 4.2f}, {2, 2, 7.8f, 1.4f, 6.0f},
       {3, 1, 6.2f, 3.2f, 3.2f}, {4, 1, 10.3f, 2.9f, 8.0f}, {4, 2, 13.0f, 3.3f, 9.5f}, {5, 1, 7.3f, 3.1f, 3.5f}},
-     {{0, 1, 7.7f, 6.2f, 0.9f}, {1, 1, 7.6f, 2.8f, 2.8f}, {2, 1, 9.1f, 4.6f, 5.0f}, {2, 2, 12.0f, 5.7f, 6.8f},
-      {3, 1, 8.0f, 3.4f, 4.7f}, {4, 1, 14.1f, 5.2f, 9.8f}, {4, 2, 17.4f, 6.3f, 11.8f}, {5, 1, 10.9f, 5.2f, 6.3f}}},
+     {{0, 1, 6.1f, 5.1f, 0.6f}, {1, 1, 6.0f, 3.3f, 1.6f}, {2, 1, 7.2f, 3.0f, 4.6f}, {2, 2, 9.2f, 3.4f, 6.0f},
+      {3, 1, 6.5f, 3.0f, 3.6f}, {4, 1, 11.4f, 3.5f, 8.6f}, {4, 2, 14.2f, 4.3f, 10.2f}, {5, 1, 8.8f, 3.6f, 4.0f},
+      {5, 2, 10.8f, 3.8f, 4.8f}},
+     {{0, 1, 7.9f, 5.9f, 1.2f}, {1, 1, 8.0f, 3.8f, 2.6f}, {2, 1, 10.2f, 5.9f, 6.1f}, {2, 2, 13.2f, 8.1f, 8.0f},
+      {3, 1, 9.6f, 5.4f, 5.6f}, {4, 1, 18.6f, 7.4f, 12.7f}, {4, 2, 23.2f, 11.7f, 14.6f}, {5, 1, 12.6f, 7.9f, 7.2f},
+      {5, 2, 15.8f, 10.7f, 9.2f}}},
 };
 
 // Class of a precision in kWinCosts.
@@ -667,51 +745,54 @@ inline int win_class(lbm_precision p)
     return p == LBM_FP64 ? 0 : p == LBM_FP32 ? 1 : p == LBM_FP32_U64 ? 2 : 3;
 }
 
-// LDS bytes of a site of a window
-template <class PR>
-constexpr int win_site_bytes()
-{
-    return 2 * (int)sizeof(typename PR::TU) + 12 * (int)sizeof(typename PR::TC) + 1;
-}
-template <class PR>
+template <class PR, int MODE, int GEN>
 constexpr bool win_fits(int s)
 {
-    return kWinShapes[s].w * kWinShapes[s].h * win_site_bytes<PR>() <= 160 * 1024;
+    constexpr int tu = (int)sizeof(typename PR::TU), tc = (int)sizeof(typename PR::TC);
+    const int n = kWinShapes[s].w * kWinShapes[s].h;
+    return n * (2 * tu + 12 * tc) + (GEN == WIN_GENERAL ? n + n / 4 * (4 + 4 * tc) : 0) + 64 <= 160 * 1024;
 }
 
-// Output rectangle of a window with rings h on a plate: the widest that fits,
-// evened out over the plate. 0 columns where the rings fill the window.
-inline WinGrid win_grid(const WinShape &s, int nx, int ny, int h, int nsteps)
+// Output nodes of a window with rings h on each side (0: none).
+inline int win_out(int n, int h) { return std::max(0, n - 2 * h); }
+
+// A rectangle of nodes.
+struct Rect {
+    int x, y, w, h;
+};
+
+// Split of a rectangle into output rectangles of at most mw x mh nodes, evened
+// out.
+inline WinRegion win_region(const Rect &r, int mw, int mh, int first)
 {
-    WinGrid g{};
-    const int mw = s.w - 2 * h, mh = s.h - 2 * h;
-    g.nsteps = nsteps;
-    if (mw <= 0 || mh <= 0) return g;
-    g.nbx = (nx + mw - 1) / mw;
-    const int nby = (ny + mh - 1) / mh;
-    g.out_w = (nx + g.nbx - 1) / g.nbx;
-    g.out_h = (ny + nby - 1) / nby;
-    g.nbx = (nx + g.out_w - 1) / g.out_w;
-    g.nb = g.nbx * ((ny + g.out_h - 1) / g.out_h);
+    const int nx = (r.w + mw - 1) / mw, ny = (r.h + mh - 1) / mh;
+    WinRegion g{r.x, r.y, r.w, r.h, (r.w + nx - 1) / nx, (r.h + ny - 1) / ny, 0, first};
+    g.nbx = (r.w + g.out_w - 1) / g.out_w;
     return g;
 }
+inline int win_blocks(const WinRegion &g) { return g.nbx * ((g.h + g.out_h - 1) / g.out_h); }
 
 // A window shape and the steps of its launches.
 struct WinChoice {
     int shape, steps;
 };
 
-// The cheapest shape per step for a plate, launches of at most max_steps
-// steps (win_reach rings each, one more with deviation storage).
-inline WinChoice choose_window(int cls, bool gen, int nx, int ny, int reach, bool dev, int max_steps)
+// The cheapest shape per step for rectangles of a plate, launches of
+// min_steps to max_steps steps (reach rings each, one more with deviation
+// storage).
+inline WinChoice choose_window(int cls, int edges, const std::vector<Rect> &rects, int reach, bool dev, int min_steps,
+                               int max_steps)
 {
-    WinChoice best{0, 1};
+    WinChoice best{0, min_steps};
     double best_t = 1e300;
-    for (const WinCost &c : kWinCosts[cls][gen ? 1 : 0]) {
-        if (c.steps < 1 || c.steps > max_steps) continue;
-        const WinGrid g = win_grid(kWinShapes[c.shape], nx, ny, c.steps * reach + (dev ? 1 : 0), c.steps);
-        if (g.nb <= 0) continue;
-        const double per_cu = (double)g.nb / 256.0, full = per_cu < 4.0 ? std::ceil(per_cu) : per_cu + 0.5;
+    for (const WinCost &c : kWinCosts[cls][edges]) {
+        if (c.steps < min_steps || c.steps > max_steps) continue;
+        const int h = c.steps * reach + (dev ? 1 : 0);
+        const int mw = win_out(kWinShapes[c.shape].w, h), mh = win_out(kWinShapes[c.shape].h, h);
+        if (!mw || !mh) continue;
+        double nb = 0;
+        for (const Rect &r : rects) nb += win_blocks(win_region(r, mw, mh, 0));
+        const double per_cu = nb / 256.0, full = per_cu < 4.0 ? std::ceil(per_cu) : per_cu + 0.5;
         const double t = std::max((double)c.lat, c.base + c.thr * full) / c.steps;
         if (t < best_t) {
             best_t = t;
@@ -727,7 +808,7 @@ hipError_t launch_window(const GenParams &p, const WinGrid &g, int shape, hipStr
     if constexpr (S < kNumWinShapes) {
         constexpr WinShape w = kWinShapes[S];
         if (shape != S) return launch_window<PR, MODE, GEN, S + 1>(p, g, shape, st);
-        if constexpr (win_fits<PR>(S)) {
+        if constexpr (win_fits<PR, MODE, GEN>(S)) {
             hipLaunchKernelGGL((window_step_kernel<PR, MODE, w.w, w.h, w.k, GEN>), dim3(g.nb),
                                dim3(w.w * w.h / w.k), 0, st, p, g);
             return hipGetLastError();
@@ -736,25 +817,18 @@ hipError_t launch_window(const GenParams &p, const WinGrid &g, int shape, hipStr
     return hipErrorInvalidConfiguration;
 }
 
-// Enqueue nsteps (1 or 2; 1 with j extrapolated) time steps with windows of
-// shape `shape` built for `edges` (WIN_*); scratch as for general_step.
+// Enqueue g.nsteps (1 or 2; 1 with j extrapolated) time steps over the
+// launch's rectangles (g.nb, g.nsteps and the list or the regions are set)
+// with windows of shape `shape` built for `edges` (WIN_*).
 template <class PR>
-hipError_t window_step(GenParams p, int edges, int shape, int nsteps, char *scratch, hipStream_t st)
+hipError_t window_step(const GenParams &p, WinGrid g, int edges, int shape, hipStream_t st)
 {
-    const int reach = p.pc ? win_reach<1>() : win_reach<0>();
-    WinGrid g = win_grid(kWinShapes[shape], p.nx, p.ny, nsteps * reach + (FStore<typename PR::TF>::kDeviation ? 1 : 0),
-                         nsteps);
-    if (g.nb <= 0 || nsteps < 1 || nsteps > kWinMaxSteps) return hipErrorInvalidConfiguration;
-    for (int s = 0; s <= nsteps; ++s)
+    if (g.nb <= 0) return hipSuccess;
+    if (g.nsteps < 1 || g.nsteps > kWinMaxSteps) return hipErrorInvalidConfiguration;
+    for (int s = 0; s <= g.nsteps; ++s)
         for (int e = 0; e < 4; ++e)
             for (int a = 0; a < 2; ++a)  // (rounded once, as the kernels' multiply-add)
                 g.uw[s][e][a] = std::fma(p.val[e][a], (double)(p.step + s), p.uwb[e][a]);
-    if (p.pc == 2) {
-        const size_t bytes = (size_t)2 * p.nx * p.ny * sizeof(typename PR::TJ);
-        const hipError_t e = hipMemcpyAsync(scratch, p.j_out, bytes, hipMemcpyDeviceToDevice, st);
-        if (e != hipSuccess) return e;
-        p.j_prev = scratch;
-    }
     if (p.pc) return edges == WIN_GENERAL  ? launch_window<PR, 1, WIN_GENERAL>(p, g, shape, st)
                      : edges == WIN_YWALLS ? launch_window<PR, 1, WIN_YWALLS>(p, g, shape, st)
                                            : launch_window<PR, 1, WIN_PERIODIC>(p, g, shape, st);
@@ -763,10 +837,10 @@ hipError_t window_step(GenParams p, int edges, int shape, int nsteps, char *scra
                                  : launch_window<PR, 0, WIN_PERIODIC>(p, g, shape, st);
 }
 
-extern template hipError_t window_step<PrecF64>(GenParams, int, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF32>(GenParams, int, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF32U64>(GenParams, int, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecF16>(GenParams, int, int, int, char *, hipStream_t);
-extern template hipError_t window_step<PrecBF16>(GenParams, int, int, int, char *, hipStream_t);
+extern template hipError_t window_step<PrecF64>(const GenParams &, WinGrid, int, int, hipStream_t);
+extern template hipError_t window_step<PrecF32>(const GenParams &, WinGrid, int, int, hipStream_t);
+extern template hipError_t window_step<PrecF32U64>(const GenParams &, WinGrid, int, int, hipStream_t);
+extern template hipError_t window_step<PrecF16>(const GenParams &, WinGrid, int, int, hipStream_t);
+extern template hipError_t window_step<PrecBF16>(const GenParams &, WinGrid, int, int, hipStream_t);
 
 }  // namespace lbm
