@@ -195,6 +195,15 @@ lbm_status lbm_read_derived(lbm_solver *h, double *sigma, double *E, double *W);
  * arrays; synchronises the stream. */
 lbm_status lbm_sample(lbm_solver *h, int n, const int *x, const int *y, double *out);
 
+/* Advance nsteps steps, sampling the nodes before the first step and after
+ * every `every` steps (and after the last): out[m][n][17] with m = 1 +
+ * ceil(nsteps / every). The steps and samples are enqueued together; the host
+ * waits once per 64 KiB of values. Limits and errors as lbm_sample and
+ * lbm_step; LBM_ERR_ARG for every < 1 with steps to do. Synchronises the
+ * stream. */
+lbm_status lbm_sample_series(lbm_solver *h, int n, const int *x, const int *y, int64_t nsteps, int64_t every,
+                             double *out);
+
 /* Launch shape of the step kernel: threads per block (64, 128, 256 or 512;
  * one lattice column per thread) and row segments per column strip
  * (1 <= n_segs <= ny). Results do not depend on it (bitwise); it only

@@ -199,11 +199,15 @@ __global__ void __launch_bounds__(256) rescale_kernel(TF *f, long long n, float 
 struct ReadParams {
     FieldParams fp;
     const void *u, *j;
-    double *out;        // staging: [values][count]
+    // u (2), v (2), P (4), sigma (4), E (4), W (1): value c of site s goes to
+    // out[group][c * plane + s * stride]; nullptr: not read
+    double *out[6];
+    size_t plane, stride;
     int y_begin;        // first row of a row read (nodes == nullptr)
     const int *nodes;   // or: site indices y * nx + x of the nodes sampled
     int count;          // sites read: rows * nx, or the number of nodes
-    int what;           // bit 0: u (2), v (2), P (4); bit 1: sigma (4), E (4), W (1)
+    const unsigned *flag;  // the plate's unstable flag, copied to flag_out
+    unsigned *flag_out;    // (nullptr: not)
     double dx;          // u = dX u_L
     double c;           // v = c j_L
     double stress;      // P, sigma, W = rho0 c^2 (lattice value)
@@ -216,6 +220,10 @@ struct ReadParams {
 //         sigma = (mu / J)(F F^T - I) + lam (J^2 - 1) / (2 J) I;
 //   E     Green-Lagrange strain (F^T F - I) / 2;
 //   W     strain-energy density of eq. (27).
+// Bound by the link to the host: with page-locked outputs the kernel writes
+// them over the link itself (55.6 GB/s, the rate of one large copy; copies of
+// 2 MiB pieces out of a staging area 45, and 40 with a wait per chunk: u, v
+// and P of 4096^2 nodes 27 ms, now 19.5).
 template <class PR>
 __global__ void __launch_bounds__(256) readout_kernel(const ReadParams p)
 {
@@ -238,40 +246,50 @@ __global__ void __launch_bounds__(256) readout_kernel(const ReadParams p)
     const TU *u = static_cast<const TU *>(p.u);
     const TJ *j = static_cast<const TJ *>(p.j);
     const size_t g = (size_t)y * fp.nx + x;
-    const size_t cp = (size_t)p.count;
+    auto put = [&](int group, int c, double v) { p.out[group][c * p.plane + s * p.stride] = v; };
+    if (s == 0 && p.flag_out) *p.flag_out = *p.flag;
     if (in_hole(fp, x, y)) {  // no material: every value reads as zero
-        const int nv = ((p.what & 1) ? 8 : 0) + ((p.what & 2) ? 9 : 0);
-        for (int k = 0; k < nv; ++k) p.out[k * cp + s] = 0.0;
+        for (int k = 0; k < 6; ++k)
+            if (p.out[k])
+                for (int c = 0; c < (k < 2 ? 2 : k < 5 ? 4 : 1); ++c) put(k, c, 0.0);
         return;
     }
     double H[4];
     grad_at(u, fp, x, y, H);
-    int k = 0;
-    if (p.what & 1) {
+    if (p.out[0]) {
+        put(0, 0, (double)u[g] * p.dx);
+        put(0, 1, (double)u[pl + g] * p.dx);
+    }
+    if (p.out[1]) {
+        put(1, 0, (double)j[g] * p.c);
+        put(1, 1, (double)j[pl + g] * p.c);
+    }
+    if (p.out[2]) {
         double P[4];
         piola<double>(H, fp.lam, fp.mu, P);
-        p.out[k++ * cp + s] = (double)u[g] * p.dx;
-        p.out[k++ * cp + s] = (double)u[pl + g] * p.dx;
-        p.out[k++ * cp + s] = (double)j[g] * p.c;
-        p.out[k++ * cp + s] = (double)j[pl + g] * p.c;
-        for (int c = 0; c < 4; ++c) p.out[k++ * cp + s] = P[c] * p.stress;
+        for (int c = 0; c < 4; ++c) put(2, c, P[c] * p.stress);
     }
-    if (p.what & 2) {
-        const double F11 = 1.0 + H[0], F12 = H[1], F21 = H[2], F22 = 1.0 + H[3];
-        const double J = F11 * F22 - F12 * F21;
-        // left Cauchy-Green B = F F^T and right C = F^T F
-        const double B11 = F11 * F11 + F12 * F12, B12 = F11 * F21 + F12 * F22, B22 = F21 * F21 + F22 * F22;
-        const double C11 = F11 * F11 + F21 * F21, C12 = F11 * F12 + F21 * F22, C22 = F12 * F12 + F22 * F22;
-        const double a = fp.mu / J, d = fp.lam * (J * J - 1.0) / (2.0 * J);
+    if (!(p.out[3] || p.out[4] || p.out[5])) return;
+    const double F11 = 1.0 + H[0], F12 = H[1], F21 = H[2], F22 = 1.0 + H[3];
+    const double J = F11 * F22 - F12 * F21;
+    // left Cauchy-Green B = F F^T and right C = F^T F
+    const double B11 = F11 * F11 + F12 * F12, B12 = F11 * F21 + F12 * F22, B22 = F21 * F21 + F22 * F22;
+    const double C11 = F11 * F11 + F21 * F21, C12 = F11 * F12 + F21 * F22, C22 = F12 * F12 + F22 * F22;
+    const double a = fp.mu / J, d = fp.lam * (J * J - 1.0) / (2.0 * J);
+    if (p.out[3]) {
         const double sg[4] = {a * (B11 - 1.0) + d, a * B12, a * B12, a * (B22 - 1.0) + d};
-        for (int c = 0; c < 4; ++c) p.out[k++ * cp + s] = sg[c] * p.stress;
-        p.out[k++ * cp + s] = 0.5 * (C11 - 1.0);
-        p.out[k++ * cp + s] = 0.5 * C12;
-        p.out[k++ * cp + s] = 0.5 * C12;
-        p.out[k++ * cp + s] = 0.5 * (C22 - 1.0);
+        for (int c = 0; c < 4; ++c) put(3, c, sg[c] * p.stress);
+    }
+    if (p.out[4]) {
+        put(4, 0, 0.5 * (C11 - 1.0));
+        put(4, 1, 0.5 * C12);
+        put(4, 2, 0.5 * C12);
+        put(4, 3, 0.5 * (C22 - 1.0));
+    }
+    if (p.out[5]) {
         const double lj = log(J);
         const double W = 0.5 * fp.mu * (C11 + C22 - 2.0) + 0.25 * fp.lam * (J * J - 1.0) - 0.5 * fp.lam * lj - fp.mu * lj;
-        p.out[k++ * cp + s] = W * p.stress;
+        put(5, 0, W * p.stress);
     }
 }
 

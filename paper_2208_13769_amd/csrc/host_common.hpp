@@ -365,7 +365,13 @@ struct PlateIO {
     double *partials;           // kMaxDiagBlocks * 8 doubles
     double *diag_out;           // 8 doubles
     hipStream_t stream;
+    // a page-locked buffer of the handle (kPinBytes) and the plate's flag, or
+    // nullptr: reads then report the flag in the buffer's first word
+    char *pin = nullptr;
+    const unsigned *flag = nullptr;
 };
+
+constexpr size_t kPinBytes = size_t(64) << 10, kPinHead = 256;  // the head holds the flag
 
 // Geometry/material view used by the start-up, read-out and diagnostics
 // kernels at step t_steps (a momentum wall is at uwb + j* t).
@@ -501,38 +507,101 @@ inline hipError_t plate_start(const PlateIO &io, const double *u0, const double 
     return hipStreamSynchronize(io.stream);
 }
 
-// u, v, P (any may be NULL) and diagnostics (out7 may be NULL) of a plate
-// after t_steps steps. Synchronises.
-// Values of read-out kind `what` (1: u, v, P; 2: sigma, E, W) of every site,
-// copied into the host planes dst[0 .. nv-1] ([ny][nx] each, NULL skips a
-// plane) through the staging area in row chunks. Synchronises.
-inline hipError_t plate_rows(const PlateIO &io, double t_steps, int what, double *const *dst, int nv)
+// Device address of a host array if its `bytes` bytes are page-locked memory
+// that the device can write, else nullptr.
+inline double *device_address(double *host, size_t bytes)
 {
-    const int nx = io.nx, ny = io.ny;
+    hipPointerAttribute_t a{}, b{};
+    char *last = reinterpret_cast<char *>(host) + bytes - 1;
+    if (hipPointerGetAttributes(&a, host) != hipSuccess || hipPointerGetAttributes(&b, last) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (a.type != hipMemoryTypeHost || b.type != hipMemoryTypeHost || !a.devicePointer ||
+        static_cast<char *>(b.devicePointer) - static_cast<char *>(a.devicePointer) != (ptrdiff_t)(bytes - 1))
+        return nullptr;
+    return static_cast<double *>(a.devicePointer);
+}
+
+// Read-out of a plate's sites without its outputs.
+inline ReadParams read_params(const PlateIO &io, double t_steps)
+{
     ReadParams rp{};
     rp.fp = field_params(io, t_steps);
     rp.u = io.u;
     rp.j = io.j;
-    rp.out = io.staging;
-    rp.nodes = nullptr;
-    rp.what = what;
     rp.dx = io.U.dx;
     rp.c = io.U.c();
     rp.stress = io.U.stress();
-    const int rows_per =
-        (int)std::max<size_t>(1, std::min<size_t>(ny, io.staging_bytes / (nv * sizeof(double) * nx)));
+    rp.stride = 1;
+    return rp;
+}
+
+inline hipError_t launch_readout(const PlateIO &io, const ReadParams &rp)
+{
+    return LBM_DISPATCH(io.prec, Kernels<PR>::readout(rp, (rp.count + 255) / 256, io.stream));
+}
+
+// Planes of a pageable array are copied together up to this many bytes: larger
+// pageable copies than 1 MiB are slower (the 256^2 FP32 request 2.85 ms with
+// copies of 1 and 2 MiB, 2.74 with 0.5).
+constexpr size_t kCopyMerge = size_t(512) << 10;
+
+// Fields of every site (dst: u, v, P, sigma, E, W, [values][ny][nx] host
+// arrays, NULL: not read). Page-locked arrays are written by the kernel, in
+// one launch; others go through the staging area in row chunks. *flagged: the flag is in io.pin.
+// Synchronises.
+inline hipError_t plate_rows(const PlateIO &io, double t_steps, double *const dst[6], bool *flagged = nullptr)
+{
+    constexpr int nv[6] = {2, 2, 4, 4, 4, 1};
+    const int nx = io.nx, ny = io.ny;
+    const size_t n = (size_t)nx * ny;
+    ReadParams rp = read_params(io, t_steps);
     hipError_t e;
+    int values = 0;  // of the arrays the kernel cannot write
+    bool direct = false;
+    for (int k = 0; k < 6; ++k) {
+        if (!dst[k]) continue;
+        rp.out[k] = device_address(dst[k], nv[k] * n * sizeof(double));
+        if (rp.out[k])
+            direct = true;
+        else
+            values += nv[k];
+    }
+    if (direct) {
+        rp.plane = n;
+        rp.count = (int)n;
+        if (flagged && io.pin) {
+            rp.flag = io.flag;
+            rp.flag_out = reinterpret_cast<unsigned *>(io.pin);
+            *flagged = true;
+        }
+        if ((e = launch_readout(io, rp))) return e;
+    }
+    if (values == 0) return hipStreamSynchronize(io.stream);
+    const int rows_per = (int)std::max<size_t>(1, std::min<size_t>(ny, io.staging_bytes / (values * sizeof(double) * nx)));
+    bool want[6];
+    for (int k = 0; k < 6; ++k) want[k] = dst[k] && !rp.out[k];
+    rp.flag_out = nullptr;
     for (int y = 0; y < ny; y += rows_per) {
         const int rows = std::min(rows_per, ny - y);
         rp.y_begin = y;
         rp.count = rows * nx;
         const size_t cnt = (size_t)rows * nx;
-        if ((e = LBM_DISPATCH(io.prec, Kernels<PR>::readout(rp, (int)((cnt + 255) / 256), io.stream)))) return e;
-        for (int k = 0; k < nv; ++k) {
-            if (!dst[k]) continue;
-            if ((e = hipMemcpyAsync(dst[k] + (size_t)y * nx, rp.out + k * cnt, cnt * sizeof(double),
-                                    hipMemcpyDeviceToHost, io.stream)))
-                return e;
+        rp.plane = cnt;
+        double *at = io.staging;
+        for (int k = 0; k < 6; ++k) {
+            rp.out[k] = want[k] ? at : nullptr;
+            if (want[k]) at += nv[k] * cnt;
+        }
+        if ((e = launch_readout(io, rp))) return e;
+        for (int k = 0; k < 6; ++k) {
+            if (!want[k]) continue;
+            const int pieces = rows == ny && nv[k] * cnt * sizeof(double) <= kCopyMerge ? 1 : nv[k];
+            for (int c = 0; c < pieces; ++c)
+                if ((e = hipMemcpyAsync(dst[k] + c * n + (size_t)y * nx, rp.out[k] + c * cnt,
+                                        (pieces == 1 ? nv[k] : 1) * cnt * sizeof(double), hipMemcpyDeviceToHost, io.stream)))
+                    return e;
         }
         if ((e = hipStreamSynchronize(io.stream))) return e;
     }
@@ -545,46 +614,59 @@ inline int sample_capacity(const PlateIO &io)
     return (int)std::min<size_t>(1 << 20, (io.staging_bytes - 256) / (17 * sizeof(double) + sizeof(int)));
 }
 
+// Enqueue the 17 values of the n nodes at `nodes` (site indices the device can
+// read) into out [n][17] that the device can write.
+inline hipError_t enqueue_sample(const PlateIO &io, double t_steps, int n, const int *nodes, double *out)
+{
+    ReadParams rp = read_params(io, t_steps);
+    constexpr int at[6] = {0, 2, 4, 8, 12, 16};
+    for (int k = 0; k < 6; ++k) rp.out[k] = out + at[k];
+    rp.plane = 1;
+    rp.stride = 17;
+    rp.nodes = nodes;
+    rp.count = n;
+    return launch_readout(io, rp);
+}
+
 // u, v, P, sigma, E, W (17 values) at the nodes (x[k], y[k]) into out[n][17].
-// The caller has checked the nodes and n <= sample_capacity(io). Synchronises.
+// The caller has checked the nodes and n <= sample_capacity(io). With the
+// handle's page-locked buffer and room in it the kernel reads the nodes from
+// it and writes the values to it: one launch and one wait (12 us) in place of
+// a pageable copy each way (54 us). Synchronises.
 inline hipError_t plate_sample(const PlateIO &io, double t_steps, int n, const int *xs, const int *ys, double *out)
 {
     if (n == 0) return hipSuccess;
+    const size_t ib = align_up((size_t)n * sizeof(int)), vb = (size_t)17 * n * sizeof(double);
+    hipError_t e;
+    if (io.pin && kPinHead + ib + vb <= kPinBytes) {
+        int *idx = reinterpret_cast<int *>(io.pin + kPinHead);
+        double *vals = reinterpret_cast<double *>(io.pin + kPinHead + ib);
+        for (int k = 0; k < n; ++k) idx[k] = ys[k] * io.nx + xs[k];
+        if ((e = enqueue_sample(io, t_steps, n, idx, vals))) return e;
+        if ((e = hipStreamSynchronize(io.stream))) return e;
+        std::copy(vals, vals + (size_t)17 * n, out);
+        return hipSuccess;
+    }
     std::vector<int> idx(n);
     for (int k = 0; k < n; ++k) idx[k] = ys[k] * io.nx + xs[k];
     int *d_idx = reinterpret_cast<int *>(io.staging);
-    double *vals = io.staging + align_up((size_t)n * sizeof(int)) / sizeof(double);
-    hipError_t e;
+    double *vals = io.staging + ib / sizeof(double);
     if ((e = hipMemcpyAsync(d_idx, idx.data(), n * sizeof(int), hipMemcpyHostToDevice, io.stream))) return e;
-    ReadParams rp{};
-    rp.fp = field_params(io, t_steps);
-    rp.u = io.u;
-    rp.j = io.j;
-    rp.out = vals;
-    rp.nodes = d_idx;
-    rp.count = n;
-    rp.what = 3;
-    rp.dx = io.U.dx;
-    rp.c = io.U.c();
-    rp.stress = io.U.stress();
-    if ((e = LBM_DISPATCH(io.prec, Kernels<PR>::readout(rp, (n + 255) / 256, io.stream)))) return e;
-    std::vector<double> tmp((size_t)17 * n);
-    if ((e = hipMemcpyAsync(tmp.data(), vals, tmp.size() * sizeof(double), hipMemcpyDeviceToHost, io.stream)))
-        return e;
-    if ((e = hipStreamSynchronize(io.stream))) return e;
-    for (int k = 0; k < n; ++k)
-        for (int c = 0; c < 17; ++c) out[(size_t)k * 17 + c] = tmp[(size_t)c * n + k];
-    return hipSuccess;
+    if ((e = enqueue_sample(io, t_steps, n, d_idx, vals))) return e;
+    if ((e = hipMemcpyAsync(out, vals, vb, hipMemcpyDeviceToHost, io.stream))) return e;
+    return hipStreamSynchronize(io.stream);
 }
 
-inline hipError_t plate_read(const PlateIO &io, double t_steps, double *u, double *v, double *P, double *out7)
+// u, v, P (any may be NULL) and diagnostics (out7 may be NULL) of a plate
+// after t_steps steps. *flagged: as plate_rows. Synchronises.
+inline hipError_t plate_read(const PlateIO &io, double t_steps, double *u, double *v, double *P, double *out7,
+                             bool *flagged = nullptr)
 {
     const size_t n = (size_t)io.nx * io.ny;
     hipError_t e;
     if (u || v || P) {
-        double *dst[8] = {u, u ? u + n : nullptr, v, v ? v + n : nullptr,
-                          P, P ? P + n : nullptr, P ? P + 2 * n : nullptr, P ? P + 3 * n : nullptr};
-        if ((e = plate_rows(io, t_steps, 1, dst, 8))) return e;
+        double *const dst[6] = {u, v, P, nullptr, nullptr, nullptr};
+        if ((e = plate_rows(io, t_steps, dst, flagged))) return e;
     }
     if (out7) {
         DiagParams dp{};
@@ -613,10 +695,8 @@ inline hipError_t plate_read(const PlateIO &io, double t_steps, double *u, doubl
 inline hipError_t plate_read_derived(const PlateIO &io, double t_steps, double *sig, double *E, double *W)
 {
     if (!sig && !E && !W) return hipSuccess;
-    const size_t n = (size_t)io.nx * io.ny;
-    double *dst[9] = {sig, sig ? sig + n : nullptr, sig ? sig + 2 * n : nullptr, sig ? sig + 3 * n : nullptr,
-                      E,   E ? E + n : nullptr,     E ? E + 2 * n : nullptr,     E ? E + 3 * n : nullptr, W};
-    return plate_rows(io, t_steps, 2, dst, 9);
+    double *const dst[6] = {nullptr, nullptr, nullptr, sig, E, W};
+    return plate_rows(io, t_steps, dst);
 }
 
 }  // namespace lbm

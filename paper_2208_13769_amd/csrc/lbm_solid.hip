@@ -103,6 +103,8 @@ struct lbm_solver {
     // fused share (forked from and joined back into the handle's stream each
     // launch); created on first use, default priority.
     hipStream_t aux = nullptr;
+    char *pin = nullptr;  // page-locked, kPinBytes; from the second read or the first sample on
+    int reads = 0;
     hipEvent_t fork = nullptr, join = nullptr;
     ~lbm_solver()
     {
@@ -110,6 +112,7 @@ struct lbm_solver {
         if (fork) (void)hipEventDestroy(fork);
         if (join) (void)hipEventDestroy(join);
         if (aux) (void)hipStreamDestroy(aux);
+        if (pin) (void)hipHostFree(pin);
     }
 
     // plates that the fused kernel's walled form cannot run whole
@@ -197,6 +200,16 @@ struct lbm_solver {
         for (int a = 0; a < 2; ++a) uwb[e][a] = now[a] - wall_speed(e, a) * n;
     }
 
+    // the page-locked buffer (its allocation costs two pageable copies); reads
+    // go without where there is none
+    void want_pin()
+    {
+        if (!pin && hipHostMalloc(reinterpret_cast<void **>(&pin), kPinBytes, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            pin = nullptr;
+        }
+    }
+
     PlateIO io() const
     {
         PlateIO p{};
@@ -229,6 +242,8 @@ struct lbm_solver {
         p.diag_out = reinterpret_cast<double *>(ws + L.small + 64);
         p.mask = mask_ptr();
         p.stream = stream;
+        p.pin = pin;
+        p.flag = flag();
         return p;
     }
 };
@@ -890,11 +905,17 @@ lbm_status lbm_read_fields(lbm_solver *h, double *u, double *v, double *P, lbm_d
     if (!h) return LBM_ERR_ARG;
     if (!h->fields) return fail(h, LBM_ERR_STATE, "no fields set");
     double out[7] = {0, 0, 0, 0, 0, 0, 0};
-    const hipError_t e = plate_read(h->io(), (double)h->steps, u, v, P, d ? out : nullptr);
+    if (h->reads++ > 0) h->want_pin();
+    bool flagged = false;
+    const hipError_t e = plate_read(h->io(), (double)h->steps, u, v, P, d ? out : nullptr, &flagged);
     if (e != hipSuccess) return hip_fail(h, e, "read-out");
     unsigned flag = 0;
-    HIP_TRY(h, hipMemcpyAsync(&flag, h->flag(), sizeof(unsigned), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
+    if (flagged) {
+        flag = *reinterpret_cast<const unsigned *>(h->pin);
+    } else {
+        HIP_TRY(h, hipMemcpyAsync(&flag, h->flag(), sizeof(unsigned), hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+    }
     if (d) {
         d->momentum[0] = out[0];
         d->momentum[1] = out[1];
@@ -992,12 +1013,48 @@ lbm_status lbm_sample(lbm_solver *h, int n, const int *x, const int *y, double *
     if (!h) return LBM_ERR_ARG;
     if (!h->fields) return fail(h, LBM_ERR_STATE, "no fields set");
     if (n < 0 || (n > 0 && (!x || !y || !out))) return fail(h, LBM_ERR_ARG, "invalid node list");
-    const PlateIO io = h->io();
-    if (n > sample_capacity(io)) return fail(h, LBM_ERR_ARG, "too many nodes for one call");
+    if (n > sample_capacity(h->io())) return fail(h, LBM_ERR_ARG, "too many nodes for one call");
     for (int k = 0; k < n; ++k)
         if (x[k] < 0 || x[k] >= h->nx || y[k] < 0 || y[k] >= h->ny) return fail(h, LBM_ERR_ARG, "node outside the plate");
-    const hipError_t e = plate_sample(io, (double)h->steps, n, x, y, out);
+    h->want_pin();
+    const hipError_t e = plate_sample(h->io(), (double)h->steps, n, x, y, out);
     if (e != hipSuccess) return hip_fail(h, e, "sample");
+    return LBM_OK;
+}
+
+lbm_status lbm_sample_series(lbm_solver *h, int n, const int *x, const int *y, int64_t nsteps, int64_t every, double *out)
+{
+    if (!h) return LBM_ERR_ARG;
+    if (every < 1 && nsteps > 0) return fail(h, LBM_ERR_ARG, "every < 1");
+    lbm_status st = lbm_sample(h, n, x, y, out);  // (checks the nodes)
+    if (st != LBM_OK) return st;
+    const int64_t m = nsteps > 0 ? (nsteps + every - 1) / every : 0;  // samples after the first
+    const size_t vb = (size_t)17 * n * sizeof(double), ib = align_up((size_t)n * sizeof(int));
+    // samples that the page-locked buffer holds at once (the nodes stand in
+    // it since the call above)
+    const size_t room = h->pin && n > 0 && kPinHead + ib + vb <= kPinBytes ? (kPinBytes - kPinHead - ib) / vb : 0;
+    int64_t got = 0;
+    while (got < m) {
+        const int64_t batch = room ? std::min<int64_t>(m - got, (int64_t)room) : 1;
+        double *vals = room ? reinterpret_cast<double *>(h->pin + kPinHead + ib) : nullptr;
+        for (int64_t q = 0; q < batch; ++q) {
+            if ((st = lbm_step(h, std::min(every, nsteps - (got + q) * every))) != LBM_OK) {
+                (void)hipStreamSynchronize(h->stream);  // samples may be on their way to the buffer
+                return st;
+            }
+            if (room)
+                HIP_TRY(h, enqueue_sample(h->io(), (double)h->steps, n, reinterpret_cast<const int *>(h->pin + kPinHead),
+                                          vals + q * 17 * (size_t)n));
+        }
+        double *to = out + (size_t)(got + 1) * 17 * n;
+        if (room) {
+            HIP_TRY(h, hipStreamSynchronize(h->stream));
+            std::copy(vals, vals + batch * 17 * (size_t)n, to);
+        } else if ((st = lbm_sample(h, n, x, y, to)) != LBM_OK) {
+            return st;
+        }
+        got += batch;
+    }
     return LBM_OK;
 }
 

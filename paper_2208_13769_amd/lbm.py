@@ -37,7 +37,8 @@ EXPORTED = [
     "lbm_set_fields", "lbm_step", "lbm_read_fields", "lbm_read_diagnostics_noalloc", "lbm_get_dt", "lbm_destroy",
     "lbm_last_error",
     "lbm_set_tiling", "lbm_get_tiling", "lbm_set_steps_per_launch", "lbm_get_steps_per_launch",
-    "lbm_resident_blocks", "lbm_set_rounding", "lbm_read_derived", "lbm_sample", "lbm_batch_read_derived",
+    "lbm_resident_blocks", "lbm_set_rounding", "lbm_read_derived", "lbm_sample", "lbm_sample_series",
+    "lbm_batch_read_derived",
     "lbm_batch_sample", "lbm_workspace_bytes_walled", "lbm_set_general_path", "lbm_set_mask",
     "lbm_batch_plate_bytes", "lbm_batch_plate_tiles", "lbm_batch_workspace_bytes", "lbm_batch_create",
     "lbm_batch_add", "lbm_batch_step", "lbm_batch_query", "lbm_batch_read", "lbm_batch_retire", "lbm_batch_info",
@@ -108,6 +109,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.lbm_read_derived.argtypes = [vp, dp, dp, dp]
     lib.lbm_sample.restype = ctypes.c_int
     lib.lbm_sample.argtypes = [vp, ctypes.c_int, ip, ip, dp]
+    lib.lbm_sample_series.restype = ctypes.c_int
+    lib.lbm_sample_series.argtypes = [vp, ctypes.c_int, ip, ip, ctypes.c_int64, ctypes.c_int64, dp]
     lib.lbm_get_dt.restype = ctypes.c_int
     lib.lbm_get_dt.argtypes = [vp, dp]
     lib.lbm_destroy.restype = None
@@ -220,6 +223,19 @@ def lbm_sample(h, xs, ys) -> np.ndarray:
         raise ValueError(f"{len(xs)} x coordinates for {len(ys)} y coordinates")
     out = np.empty((len(xs), 17))
     _check(load_library().lbm_sample(h, len(xs), _iptr(xs), _iptr(ys), _dptr(out)), h)
+    return out
+
+
+def lbm_sample_series(h, xs, ys, nsteps: int, every: int) -> np.ndarray:
+    """[m][n][17] values at the nodes before the first step and after every
+    `every` steps of nsteps."""
+    xs = np.ascontiguousarray(xs, dtype=np.int32).ravel()
+    ys = np.ascontiguousarray(ys, dtype=np.int32).ravel()
+    if len(xs) != len(ys):
+        raise ValueError(f"{len(xs)} x coordinates for {len(ys)} y coordinates")
+    m = 1 + (-(-nsteps // every) if nsteps > 0 and every > 0 else 0)
+    out = np.empty((m, len(xs), 17))
+    _check(load_library().lbm_sample_series(h, len(xs), _iptr(xs), _iptr(ys), nsteps, every, _dptr(out)), h)
     return out
 
 
@@ -399,17 +415,9 @@ class Solver:
         """Advance nsteps, sampling the nodes before the first step and after
         every `every` steps: returns (steps since the call [m], values
         [m][n][17])."""
-        steps, vals = [], []
-        done = 0
-        while True:
-            steps.append(done)
-            vals.append(self.sample(xs, ys))
-            if done >= nsteps:
-                break
-            k = min(every, nsteps - done)
-            self.step(k)
-            done += k
-        return np.array(steps), np.array(vals)
+        nsteps, every = int(nsteps), int(every)
+        vals = lbm_sample_series(self.h, xs, ys, nsteps, every)
+        return np.minimum(np.arange(len(vals)) * every, max(nsteps, 0)), vals
 
     def read(self, want_fields: bool = True):
         """Return (u, v, P, Diagnostics, status)."""
