@@ -374,18 +374,26 @@ __global__ void __launch_bounds__(256) diag_kernel(const DiagParams p)
     if (threadIdx.x < 7) p.partials[blockIdx.x * 8 + threadIdx.x] = red[threadIdx.x][0];
 }
 
-// Second stage: one block folds the per-block partials in index order.
-static __global__ void __launch_bounds__(64) diag_final_kernel(const double *partials, int nblocks, double *out)
+// Second stage: one block folds the per-block partials in index order, one
+// thread per value from LDS (one thread reading memory value by value took
+// 58 us for 256 blocks).
+static __global__ void __launch_bounds__(256) diag_final_kernel(const double *partials, int nblocks, double *out)
 {
-    if (threadIdx.x != 0) return;
-    double acc[7] = {0, 0, 0, 0, 1e300, 0, 0};
-    for (int b = 0; b < nblocks; ++b) {
-        for (int k = 0; k < 4; ++k) acc[k] += partials[b * 8 + k];
-        acc[4] = fmin(acc[4], partials[b * 8 + 4]);
-        acc[5] = fmax(acc[5], partials[b * 8 + 5]);
-        acc[6] = fmax(acc[6], partials[b * 8 + 6]);
+    __shared__ double part[256][8];
+    const int k = threadIdx.x;
+    double acc = k == 4 ? 1e300 : 0.0;
+    for (int b0 = 0; b0 < nblocks; b0 += 256) {
+        const int n = min(256, nblocks - b0);
+        __syncthreads();
+        for (int i = threadIdx.x; i < 8 * n; i += 256) part[i >> 3][i & 7] = partials[(size_t)b0 * 8 + i];
+        __syncthreads();
+        if (k < 7)
+            for (int b = 0; b < n; ++b) {
+                const double v = part[b][k];
+                acc = k < 4 ? acc + v : k == 4 ? fmin(acc, v) : fmax(acc, v);
+            }
     }
-    for (int k = 0; k < 7; ++k) out[k] = acc[k];
+    if (k < 7) out[k] = acc;
 }
 
 }  // namespace lbm

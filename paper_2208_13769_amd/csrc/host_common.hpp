@@ -683,7 +683,7 @@ inline hipError_t plate_read(const PlateIO &io, double t_steps, double *u, doubl
         dp.partials = io.partials;
         const int nblocks = (int)std::min<size_t>(kMaxDiagBlocks, (n + 255) / 256);
         if ((e = LBM_DISPATCH(io.prec, Kernels<PR>::diag(dp, nblocks, io.stream)))) return e;
-        hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(64), 0, io.stream, io.partials, nblocks, io.diag_out);
+        hipLaunchKernelGGL(diag_final_kernel, dim3(1), dim3(256), 0, io.stream, io.partials, nblocks, io.diag_out);
         if ((e = hipGetLastError())) return e;
         if ((e = hipMemcpyAsync(out7, io.diag_out, 7 * sizeof(double), hipMemcpyDeviceToHost, io.stream))) return e;
         if ((e = hipStreamSynchronize(io.stream))) return e;
