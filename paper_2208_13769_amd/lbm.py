@@ -186,7 +186,14 @@ def lbm_set_body_force(h, b):
     _check(load_library().lbm_set_body_force(h, _dptr(b)), h)
 
 
+_Pair = ctypes.c_double * 2
+
+
 def lbm_set_boundary(h, edge, bc, value=None):
+    if type(value) is tuple and len(value) == 2 and type(value[0]) is type(value[1]) is float:
+        # (a load history sets an edge before every step: 0.6 us against 3.5)
+        _check(load_library().lbm_set_boundary(h, edge, bc, _Pair(*value)), h)
+        return
     v = None if value is None else np.ascontiguousarray(value, dtype=np.float64).ravel()
     if v is not None and v.size != 2:
         raise ValueError(f"boundary value of {v.size} values; expected 2")
