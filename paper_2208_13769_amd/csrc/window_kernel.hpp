@@ -672,10 +672,10 @@ __global__ void __launch_bounds__(WW *WH / K) window_step_kernel(const GenParams
         const int4 e = g.list[tile];
         x0 = e.x, y0 = e.y, ow = e.z, oh = e.w;
     } else {
-        int q = 0;
-        for (int k = 1; k < g.n_regions; ++k)
-            if (tile >= g.reg[k].first) q = k;
-        const WinRegion &r = g.reg[q];
+        WinRegion r = g.reg[0];
+        if (g.n_regions > 1)
+            for (int k = 1; k < g.n_regions; ++k)
+                if (tile >= g.reg[k].first) r = g.reg[k];
         const int t = tile - r.first, ty = t / r.nbx, tx = t - ty * r.nbx;
         x0 = r.x + tx * r.out_w;
         y0 = r.y + ty * r.out_h;
@@ -694,8 +694,9 @@ constexpr WinShape kWinShapes[] = {{16, 16, 1}, {32, 16, 1}, {32, 32, 1}, {64, 1
 constexpr int kNumWinShapes = (int)(sizeof(kWinShapes) / sizeof(kWinShapes[0]));
 
 // Cost of a launch of n blocks with a shape and a number of steps, in us:
-// at least lat (up to one block per compute unit), base + thr per block on
-// the fullest compute unit beyond. Measured with plates of 16 to 2048 full
+// lat for a few blocks to lat1 for one per compute unit, base + thr per block
+// on the fullest compute unit beyond (its number is rounded up, half way below
+// two per compute unit, not at all from four). Measured with plates of 16 to 2048 full
 // windows, per class (double; float; float with a double displacement; 16-bit
 // storage) and kind of edges (WIN_*). A two-step
 // launch pays where the plate is small enough that the launch itself and the
@@ -703,40 +704,46 @@ constexpr int kNumWinShapes = (int)(sizeof(kWinShapes) / sizeof(kWinShapes[0]));
 // steps, 4.3 with 16 x 16 and 7.0 with 32 x 32 windows of one step).
 struct WinCost {
     int shape, steps;
-    float lat, base, thr;
+    float lat, lat1, base, thr;
 };
 constexpr int kNumWinCosts = 9;
 constexpr WinCost kWinCosts[4][3][kNumWinCosts] = {
-    {{{0, 1, 4.4f, 3.3f, 0.9f}, {1, 1, 5.6f, 2.3f, 2.4f}, {2, 1, 9.0f, 3.3f, 7.2f}, {2, 2, 9.8f, 3.0f, 7.3f},
-      {3, 1, 8.4f, 1.6f, 5.8f}, {5, 1, 9.4f, 3.2f, 7.5f}},
-     {{0, 1, 5.6f, 4.3f, 1.0f}, {1, 1, 6.3f, 2.9f, 2.5f}, {2, 1, 9.8f, 3.6f, 7.4f}, {2, 2, 10.4f, 3.4f, 7.7f},
-      {3, 1, 8.8f, 2.1f, 6.0f}, {5, 1, 10.9f, 4.1f, 8.1f}, {5, 2, 11.8f, 4.3f, 8.5f}},
-     {{0, 1, 6.9f, 4.7f, 1.7f}, {1, 1, 8.2f, 5.0f, 4.2f}, {2, 1, 15.9f, 5.6f, 11.6f}, {2, 2, 19.6f, 7.8f, 13.4f},
-      {3, 1, 14.1f, 7.2f, 9.3f}, {5, 1, 13.7f, 5.7f, 9.1f}, {5, 2, 17.1f, 10.3f, 10.4f}}},
-    {{{0, 1, 3.9f, 3.2f, 0.5f}, {1, 1, 4.4f, 3.2f, 1.0f}, {2, 1, 6.1f, 2.2f, 3.2f}, {2, 2, 6.6f, 2.9f, 3.0f},
-      {3, 1, 5.6f, 2.1f, 2.4f}, {4, 1, 10.0f, 5.2f, 7.1f}, {4, 2, 11.1f, 2.4f, 7.9f}, {5, 1, 6.8f, 2.4f, 3.3f}},
-     {{0, 1, 5.2f, 4.2f, 0.5f}, {1, 1, 5.3f, 3.4f, 1.3f}, {2, 1, 6.7f, 2.6f, 4.0f}, {2, 2, 7.7f, 2.9f, 4.9f},
-      {3, 1, 6.1f, 2.6f, 2.6f}, {4, 1, 10.9f, 5.4f, 7.6f}, {4, 2, 11.9f, 3.3f, 8.4f}, {5, 1, 7.8f, 3.3f, 3.4f},
-      {5, 2, 9.3f, 2.2f, 4.3f}},
-     {{0, 1, 6.5f, 4.8f, 1.0f}, {1, 1, 6.9f, 3.5f, 2.2f}, {2, 1, 8.8f, 5.1f, 5.1f}, {2, 2, 11.2f, 7.3f, 6.4f},
-      {3, 1, 8.2f, 4.8f, 4.5f}, {4, 1, 13.7f, 5.6f, 9.8f}, {4, 2, 17.4f, 9.8f, 10.5f}, {5, 1, 10.6f, 6.2f, 6.3f},
-      {5, 2, 13.5f, 8.0f, 8.2f}}},
-    {{{0, 1, 3.9f, 3.3f, 0.5f}, {1, 1, 4.5f, 3.4f, 1.0f}, {2, 1, 6.6f, 2.6f, 3.4f}, {2, 2, 7.2f, 3.0f, 3.4f},
-      {3, 1, 6.1f, 2.0f, 2.8f}, {4, 1, 11.4f, 0.0f, 11.1f}, {4, 2, 12.6f, 2.2f, 9.2f}, {5, 1, 7.2f, 2.7f, 3.7f}},
-     {{0, 1, 5.2f, 4.3f, 0.6f}, {1, 1, 5.4f, 3.4f, 1.4f}, {2, 1, 7.2f, 2.5f, 4.5f}, {2, 2, 8.2f, 2.9f, 5.3f},
-      {3, 1, 6.5f, 2.4f, 3.7f}, {4, 1, 12.1f, 0.6f, 11.3f}, {4, 2, 13.4f, 2.8f, 9.8f}, {5, 1, 8.2f, 3.6f, 3.7f},
-      {5, 2, 9.5f, 2.4f, 4.7f}},
-     {{0, 1, 6.5f, 4.9f, 1.0f}, {1, 1, 7.1f, 3.6f, 2.3f}, {2, 1, 9.3f, 5.2f, 5.4f}, {2, 2, 11.5f, 7.4f, 6.9f},
-      {3, 1, 8.7f, 5.2f, 4.7f}, {4, 1, 15.5f, 2.7f, 12.9f}, {4, 2, 19.3f, 10.9f, 11.5f}, {5, 1, 11.0f, 6.5f, 6.5f},
-      {5, 2, 14.3f, 9.5f, 8.2f}}},
-    {{{0, 1, 4.3f, 3.5f, 0.6f}, {1, 1, 4.5f, 2.9f, 1.3f}, {2, 1, 6.3f, 2.3f, 4.2f}, {2, 2, 7.8f, 1.4f, 6.0f},
-      {3, 1, 6.2f, 3.2f, 3.2f}, {4, 1, 10.3f, 2.9f, 8.0f}, {4, 2, 13.0f, 3.3f, 9.5f}, {5, 1, 7.3f, 3.1f, 3.5f}},
-     {{0, 1, 6.1f, 5.1f, 0.6f}, {1, 1, 6.0f, 3.3f, 1.6f}, {2, 1, 7.2f, 3.0f, 4.6f}, {2, 2, 9.2f, 3.4f, 6.0f},
-      {3, 1, 6.5f, 3.0f, 3.6f}, {4, 1, 11.4f, 3.5f, 8.6f}, {4, 2, 14.2f, 4.3f, 10.2f}, {5, 1, 8.8f, 3.6f, 4.0f},
-      {5, 2, 10.8f, 3.8f, 4.8f}},
-     {{0, 1, 7.9f, 5.9f, 1.2f}, {1, 1, 8.0f, 3.8f, 2.6f}, {2, 1, 10.2f, 5.9f, 6.1f}, {2, 2, 13.2f, 8.1f, 8.0f},
-      {3, 1, 9.6f, 5.4f, 5.6f}, {4, 1, 18.6f, 7.4f, 12.7f}, {4, 2, 23.2f, 11.7f, 14.6f}, {5, 1, 12.6f, 7.9f, 7.2f},
-      {5, 2, 15.8f, 10.7f, 9.2f}}},
+    {{{0, 1, 4.7f, 4.8f, 3.8f, 0.9f}, {1, 1, 5.4f, 6.1f, 2.9f, 2.4f}, {2, 1, 7.7f, 9.6f, 3.7f, 7.2f},
+      {2, 2, 8.8f, 10.2f, 2.8f, 7.6f}, {3, 1, 6.5f, 8.8f, 2.2f, 5.8f}, {5, 1, 7.8f, 9.7f, 3.4f, 7.6f},
+      {5, 2, 9.1f, 10.6f, 3.2f, 7.9f}},
+     {{0, 1, 5.8f, 5.8f, 4.3f, 1.0f}, {1, 1, 6.3f, 6.3f, 3.0f, 2.5f}, {2, 1, 8.2f, 9.8f, 3.7f, 7.4f},
+      {2, 2, 9.4f, 10.4f, 3.2f, 7.7f}, {3, 1, 7.0f, 8.8f, 2.0f, 6.0f}, {5, 1, 9.3f, 10.8f, 4.2f, 8.0f},
+      {5, 2, 11.1f, 11.8f, 3.7f, 8.6f}},
+     {{0, 1, 7.1f, 7.1f, 4.7f, 1.6f}, {1, 1, 7.8f, 8.2f, 4.9f, 4.2f}, {2, 1, 12.4f, 15.8f, 5.9f, 11.5f},
+      {2, 2, 16.8f, 19.6f, 8.7f, 13.3f}, {3, 1, 11.1f, 14.2f, 7.0f, 9.3f}, {5, 1, 12.0f, 13.8f, 5.8f, 9.2f},
+      {5, 2, 16.2f, 17.1f, 10.3f, 10.4f}}},
+    {{{0, 1, 4.3f, 4.3f, 3.7f, 0.5f}, {1, 1, 4.5f, 4.8f, 3.6f, 1.0f}, {2, 1, 5.7f, 6.5f, 2.5f, 3.2f},
+      {2, 2, 6.5f, 7.1f, 3.3f, 3.0f}, {3, 1, 5.1f, 5.9f, 2.3f, 2.5f}, {4, 1, 7.3f, 10.2f, 5.6f, 7.1f},
+      {4, 2, 8.7f, 11.3f, 2.3f, 8.0f}, {5, 1, 6.2f, 7.0f, 2.5f, 3.4f}, {5, 2, 7.3f, 7.8f, 3.1f, 3.4f}},
+     {{0, 1, 5.3f, 5.3f, 4.3f, 0.5f}, {1, 1, 5.5f, 5.5f, 3.4f, 1.3f}, {2, 1, 6.3f, 6.8f, 2.5f, 4.1f},
+      {2, 2, 7.7f, 7.8f, 2.9f, 4.9f}, {3, 1, 5.7f, 6.1f, 2.1f, 2.8f}, {4, 1, 8.2f, 10.8f, 6.1f, 7.5f},
+      {4, 2, 10.0f, 11.9f, 3.0f, 8.5f}, {5, 1, 7.5f, 7.8f, 3.2f, 3.5f}, {5, 2, 9.5f, 9.5f, 2.3f, 4.2f}},
+     {{0, 1, 6.7f, 6.7f, 4.9f, 0.9f}, {1, 1, 6.9f, 6.9f, 3.5f, 2.1f}, {2, 1, 8.2f, 8.8f, 5.0f, 5.1f},
+      {2, 2, 10.9f, 11.1f, 7.6f, 6.3f}, {3, 1, 7.5f, 8.2f, 4.9f, 4.4f}, {4, 1, 11.6f, 13.8f, 5.4f, 9.8f},
+      {4, 2, 15.5f, 17.5f, 10.3f, 10.2f}, {5, 1, 10.2f, 10.6f, 6.4f, 6.2f}, {5, 2, 13.7f, 13.7f, 9.0f, 7.9f}}},
+    {{{0, 1, 4.4f, 4.4f, 3.8f, 0.5f}, {1, 1, 4.6f, 5.0f, 3.9f, 1.0f}, {2, 1, 5.9f, 7.0f, 2.5f, 3.7f},
+      {2, 2, 6.9f, 7.5f, 3.3f, 3.4f}, {3, 1, 5.2f, 6.5f, 2.2f, 2.9f}, {4, 1, 8.2f, 11.5f, 0.1f, 11.0f},
+      {4, 2, 9.8f, 12.8f, 2.3f, 9.2f}, {5, 1, 6.4f, 7.5f, 2.7f, 3.8f}, {5, 2, 7.6f, 8.2f, 3.2f, 3.8f}},
+     {{0, 1, 5.5f, 5.5f, 4.3f, 0.6f}, {1, 1, 5.6f, 5.6f, 3.5f, 1.4f}, {2, 1, 6.5f, 7.2f, 2.5f, 4.5f},
+      {2, 2, 8.0f, 8.2f, 3.2f, 5.2f}, {3, 1, 5.8f, 6.5f, 2.4f, 3.7f}, {4, 1, 8.9f, 12.1f, 0.2f, 11.5f},
+      {4, 2, 11.0f, 13.4f, 2.6f, 9.9f}, {5, 1, 7.7f, 8.2f, 3.7f, 3.7f}, {5, 2, 9.8f, 9.8f, 2.6f, 4.6f}},
+     {{0, 1, 6.8f, 6.8f, 4.9f, 1.0f}, {1, 1, 7.0f, 7.0f, 3.7f, 2.3f}, {2, 1, 8.5f, 9.3f, 5.0f, 5.4f},
+      {2, 2, 11.3f, 11.6f, 7.8f, 6.7f}, {3, 1, 7.7f, 8.6f, 5.3f, 4.6f}, {4, 1, 12.5f, 15.4f, 2.4f, 12.9f},
+      {4, 2, 16.6f, 19.0f, 10.7f, 11.4f}, {5, 1, 10.5f, 11.0f, 6.7f, 6.5f}, {5, 2, 14.2f, 14.2f, 9.1f, 8.3f}}},
+    {{{0, 1, 4.5f, 4.6f, 3.8f, 0.6f}, {1, 1, 4.5f, 4.8f, 3.0f, 1.3f}, {2, 1, 5.8f, 6.6f, 2.5f, 4.2f},
+      {2, 2, 7.5f, 8.0f, 2.3f, 5.7f}, {3, 1, 5.3f, 6.3f, 3.4f, 3.3f}, {4, 1, 8.6f, 10.5f, 3.4f, 7.9f},
+      {4, 2, 10.6f, 13.2f, 3.7f, 9.5f}, {5, 1, 6.9f, 7.5f, 3.3f, 3.6f}, {5, 2, 8.6f, 9.0f, 3.6f, 4.3f}},
+     {{0, 1, 6.3f, 6.3f, 5.1f, 0.6f}, {1, 1, 6.1f, 6.1f, 3.4f, 1.6f}, {2, 1, 7.0f, 7.3f, 3.2f, 4.6f},
+      {2, 2, 9.4f, 9.4f, 3.4f, 6.0f}, {3, 1, 6.3f, 6.5f, 3.4f, 3.5f}, {4, 1, 9.6f, 11.3f, 3.4f, 8.6f},
+      {4, 2, 12.1f, 14.2f, 3.9f, 10.5f}, {5, 1, 8.9f, 8.9f, 3.8f, 3.9f}, {5, 2, 11.2f, 11.2f, 3.8f, 4.8f}},
+     {{0, 1, 8.2f, 8.2f, 6.2f, 1.1f}, {1, 1, 8.1f, 8.1f, 3.9f, 2.6f}, {2, 1, 9.7f, 10.2f, 5.7f, 6.1f},
+      {2, 2, 12.9f, 13.0f, 7.6f, 8.1f}, {3, 1, 9.0f, 9.6f, 5.7f, 5.5f}, {4, 1, 15.6f, 18.6f, 7.5f, 12.6f},
+      {4, 2, 20.0f, 23.1f, 11.9f, 14.5f}, {5, 1, 12.4f, 12.4f, 7.3f, 7.2f}, {5, 2, 15.9f, 15.9f, 10.3f, 9.3f}}},
 };
 
 // Class of a precision in kWinCosts.
@@ -792,8 +799,11 @@ inline WinChoice choose_window(int cls, int edges, const std::vector<Rect> &rect
         if (!mw || !mh) continue;
         double nb = 0;
         for (const Rect &r : rects) nb += win_blocks(win_region(r, mw, mh, 0));
-        const double per_cu = nb / 256.0, full = per_cu < 4.0 ? std::ceil(per_cu) : per_cu + 0.5;
-        const double t = std::max((double)c.lat, c.base + c.thr * full) / c.steps;
+        const double per_cu = nb / 256.0, full = per_cu < 2.0   ? 0.5 * (per_cu + std::ceil(per_cu))
+                                                       : per_cu < 4.0 ? std::ceil(per_cu)
+                                                                      : per_cu;
+        const double one = c.lat + (c.lat1 - c.lat) * std::min(1.0, per_cu);
+        const double t = (per_cu <= 1.0 ? one : std::max(one, c.base + c.thr * full)) / c.steps;
         if (t < best_t) {
             best_t = t;
             best = WinChoice{c.shape, c.steps};
