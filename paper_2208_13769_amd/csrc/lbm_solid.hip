@@ -74,7 +74,7 @@ struct lbm_solver {
     hipStream_t stream = nullptr;
     Layout L{};
     int cur = 0;  // copy holding the current state
-    int jslot = 0;  // buffer of the current j (j extrapolated)
+    int jslot = 0, jback = 1;  // buffers of the current j and of the one before it (j extrapolated)
     bool material = false, fields = false;
     double rho0 = 1, lam = 0, mu = 0, tau = 1;
     double body[2] = {0, 0};
@@ -159,12 +159,12 @@ struct lbm_solver {
     void *fptr(int c) const { return ws + L.state.f[c]; }
     void *uptr(int c) const { return ws + L.state.u[c]; }
     // With j extrapolated a step reads j of the two states before it while it
-    // writes the next: three buffers take turns, jslot holding the current one
-    // and the one before it that of copy cur ^ 1.
-    void *jbuf(int k) const { return k % 3 == 2 ? ws + L.scratch : ws + L.state.j[k % 3]; }
+    // writes the next: three buffers take turns.
+    void *jbuf(int k) const { return k == 2 ? ws + L.scratch : ws + L.state.j[k]; }
+    int jfree() const { return 3 - jslot - jback; }
     void *jptr(int c) const
     {
-        return scheme == LBM_SCHEME_EXTRAP ? jbuf(c == cur ? jslot : jslot + 2) : ws + L.state.j[c];
+        return scheme == LBM_SCHEME_EXTRAP ? jbuf(c == cur ? jslot : jback) : ws + L.state.j[c];
     }
     unsigned *flag() const { return reinterpret_cast<unsigned *>(ws + L.small); }
     Units units() const { return Units{dx, rho0, lam, mu}; }
@@ -703,6 +703,7 @@ lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0)
     if (!h->material) return fail(h, LBM_ERR_STATE, "set the material before the fields");
     h->cur = 0;
     h->jslot = 0;
+    h->jback = 1;
     for (auto &w : h->uwb) w[0] = w[1] = 0.0;  // every wall starts undisplaced
     double scale = 1.0;
     bool nonfinite = false;
@@ -746,6 +747,14 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     sp.seed = h->seed;
     const int nblocks = h->shape.n_strips * h->shape.n_segs;
     const bool pc = h->scheme == LBM_SCHEME_PC;
+    // Under capture a call leaves the state in the buffers that one launch per
+    // step leaves it in, so that a graph of an even number of steps can be
+    // replayed: an even number of two-step launches, and two buffers of j with a
+    // copy of the older one (the rotation of three comes round after six steps).
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
+    const bool captured = capture == hipStreamCaptureStatusActive;
+    const int64_t paired = captured ? nsteps / 4 * 4 : nsteps / 2 * 2;  // steps that two-step launches may take
     auto advance = [&](auto &p) {  // state pointers and index of the next launch
         p.f_in = h->fptr(h->cur);
         p.u_in = h->uptr(h->cur);
@@ -757,7 +766,9 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     };
     auto done = [&](int n) {
         h->cur ^= 1;
-        h->jslot = (h->jslot + 1) % 3;
+        const int next = captured ? h->jback : h->jfree();
+        h->jback = h->jslot;
+        h->jslot = next;
         h->steps += n;
     };
     const bool whole_windows = h->windows();
@@ -796,21 +807,30 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         auto windows = [&](const WinGrid &g, int shape, int form, hipStream_t st) {
             return LBM_DISPATCH(h->prec, window_step<PR>(gp, g, form, shape, st));
         };
-        auto next = [&]() {
+        auto next = [&]() -> hipError_t {
             advance(gp);
-            if (gp.pc == 2) {  // j of the step before, and the third buffer
-                gp.j_prev = gp.j_out;
-                gp.j_out = h->jbuf(h->jslot + 1);
+            if (gp.pc != 2) return hipSuccess;
+            gp.j_prev = gp.j_out;  // j of the step before, and the third buffer
+            void *const third = h->jbuf(h->jfree());
+            if (!captured) {
+                gp.j_out = third;
+                return hipSuccess;
             }
+            gp.j_prev = third;
+            return hipMemcpyAsync(third, gp.j_out, 2 * (size_t)h->nx * h->ny * elem_sizes(h->prec).j,
+                                  hipMemcpyDeviceToDevice, h->stream);
         };
         if (split) {
             // The fused kernel's periodic form over the part of the plate
             // clear of walls and holes, windows over the rest: both read the
             // state of step n and write disjoint sites of the new one.
             for (int n = max_steps_per_launch(h->prec, h->scheme); n >= 1; --n) {
-                if (nsteps - k < n) continue;
+                const int64_t end = n == 2 ? paired : nsteps;
+                if (end - k < n) continue;
                 // y walls alone, one step: the fused kernel's walled form (below)
                 if (n == 1 && !h->split_edges() && gp.pc != 2) continue;
+                // the upload of a mask's lists waits for the stream
+                if (captured && h->has_mask && !h->split[n - 1].built) continue;
                 HIP_TRY(h, plan_split(h, n));
                 const SplitPlan &p = h->split[n - 1];
                 if (!p.use) continue;
@@ -831,9 +851,9 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
                     HIP_TRY(h, hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));
                     HIP_TRY(h, hipEventCreateWithFlags(&h->join, hipEventDisableTiming));
                 }
-                for (; k + n <= nsteps; k += n) {
+                for (; k + n <= end; k += n) {
                     advance(fp);
-                    next();
+                    HIP_TRY(h, next());
                     if (beside) {
                         HIP_TRY(h, hipEventRecord(h->fork, h->stream));
                         HIP_TRY(h, hipStreamWaitEvent(h->aux, h->fork, 0));
@@ -861,15 +881,16 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
             const bool dev = deviation_storage(h->prec);
             while (k < nsteps) {
                 const WinChoice c = choose_window(win_class(h->prec), edges, plate, reach, dev, 1,
-                                                  nsteps - k >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
+                                                  paired - k >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
                 const int hh = c.steps * reach + (dev ? 1 : 0);
                 WinGrid g{};
                 g.nsteps = c.steps;
                 g.n_regions = 1;
                 g.reg[0] = win_region(plate[0], win_out(kWinShapes[c.shape].w, hh), win_out(kWinShapes[c.shape].h, hh), 0);
                 g.nb = win_blocks(g.reg[0]);
-                for (; k + c.steps <= nsteps; k += c.steps) {
-                    next();
+                const int64_t end = c.steps > 1 ? paired : nsteps;
+                for (; k + c.steps <= end; k += c.steps) {
+                    HIP_TRY(h, next());
                     HIP_TRY(h, windows(g, c.shape, edges, h->stream));
                     done(c.steps);
                 }
@@ -886,7 +907,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         sp2.n_strips = shape.n_strips;
         sp2.n_segs = shape.n_segs;
         const int nb2 = shape.n_strips * shape.n_segs;
-        for (; k + 2 <= nsteps; k += 2) {
+        for (const int64_t end = pairs ? paired : nsteps; k + 2 <= end; k += 2) {
             advance(sp2);
             HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2(sp2, shape.block, nb2, h->stream)));
             done(2);
