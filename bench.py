@@ -212,7 +212,7 @@ def general_source_hash() -> str:
 def general_traffic_for(precision: str, n: int):
     """HBM bytes per step of the hole workload from the committed rocprofv3
     counter record, if it was taken on the current source at this size."""
-    path = os.path.join(ROOT, "profiles", f"tile_step_{precision}_{n}_hole_counters.txt")
+    path = os.path.join(ROOT, "profiles", f"general_{precision}_{n}_hole_counters.txt")
     if not os.path.exists(path):
         return None
     with open(path) as fh:
@@ -283,7 +283,7 @@ def bench_hole(args):
                      "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
                      "kernel": "general step: the fused kernel over the share clear of walls and the hole "
                                "(step2_list_kernel, two steps per launch, with 32/64-bit populations; else "
-                               "step_list_kernel) beside tile_step_kernel on a second stream (traffic: HBM bytes "
+                               "step_list_kernel) beside window_step_kernel on a second stream (traffic: HBM bytes "
                                "per step)",
                      "bytes_per_material_site": per_site},
         "run": {"status": int(st), "min_J": d.min_J, "max_strain": d.max_strain},
@@ -521,7 +521,7 @@ def main():
     mlups = sites * args.steps / (ms / 1e3) / 1e6
     roofline = step_roofline(prec, sites, spl, ms_step,
                              None if general else traffic_for(prec, sites, block, segs, spl),
-                             "tile_step_kernel" if general else None)
+                             "window_step_kernel" if general else None)
 
     out = {
         "metric": METRIC, "value": round(mlups, 1), "unit": "MLUPS", "n_gpus": 1, "steps": args.steps,

@@ -132,8 +132,8 @@ lbm_status lbm_set_body_force(lbm_solver *h, const double b[2]);
  * of a periodic pair a wall turns the other into a momentum wall at rest
  * until it is set). value may be NULL for LBM_BC_PERIODIC. Takes effect from
  * the next lbm_step, so a load history can be applied step by step.
- * Walls on the x edges run the general step (one launch of 2D tiles with
- * walls and corners on every edge) and need a workspace of
+ * Walls on the x edges run the general step (2D windows with walls and
+ * corners on every edge, beside the fused kernel on large plates) and need a workspace of
  * lbm_workspace_bytes_walled() bytes
  * (LBM_ERR_NOMEM otherwise). At a corner of two walls the diagonal link takes
  * the momentum wall's rule if either wall is one (the mean j* if both are);
