@@ -117,7 +117,7 @@ struct lbm_batch {
     PlateDesc *h_plates[2] = {nullptr, nullptr};
     TileDesc *h_tiles[2] = {nullptr, nullptr};
     int *h_ntiles[2] = {nullptr, nullptr};
-    char *h_pin = nullptr;  // page-locked buffer of the read-outs
+    char *h_pin = nullptr;  // page-locked: buffer of the read-outs, then the tables' copies
     hipEvent_t ev[2] = {nullptr, nullptr};
     bool ev_used[2] = {false, false};
     int buf = 0;
@@ -381,13 +381,18 @@ lbm_status lbm_batch_create(int max_plates, int max_tiles, lbm_precision p, lbm_
     b->free_list[0] = b->arena_bytes;
     b->slots.resize(max_plates);
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 2 && e == hipSuccess; ++i) {
-        e = hipHostMalloc((void **)&b->h_plates[i], sizeof(PlateDesc) * max_plates, hipHostMallocDefault);
-        if (!e) e = hipHostMalloc((void **)&b->h_tiles[i], sizeof(TileDesc) * max_tiles, hipHostMallocDefault);
-        if (!e) e = hipHostMalloc((void **)&b->h_ntiles[i], sizeof(int), hipHostMallocDefault);
-        if (!e) e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
+    // one page-locked allocation for the tables' copies and the read-outs (an
+    // allocation takes tens of microseconds whatever its size)
+    const size_t plates_b = align_up(sizeof(PlateDesc) * max_plates), tiles_b = align_up(sizeof(TileDesc) * max_tiles);
+    const size_t half = plates_b + tiles_b + kAlign;
+    e = hipHostMalloc((void **)&b->h_pin, kPinBytes + 2 * half, hipHostMallocDefault);
+    for (int i = 0; i < 2 && !e; ++i) {
+        char *const at = b->h_pin + kPinBytes + i * half;
+        b->h_plates[i] = reinterpret_cast<PlateDesc *>(at);
+        b->h_tiles[i] = reinterpret_cast<TileDesc *>(at + plates_b);
+        b->h_ntiles[i] = reinterpret_cast<int *>(at + plates_b + tiles_b);
+        e = hipEventCreateWithFlags(&b->ev[i], hipEventDisableTiming);
     }
-    if (!e) e = hipHostMalloc((void **)&b->h_pin, kPinBytes, hipHostMallocDefault);
     if (!e) e = hipStreamCreateWithFlags(&b->capture, hipStreamNonBlocking);
     int dev = 0, cus = 0;
     if (!e) e = hipGetDevice(&dev);
@@ -787,12 +792,8 @@ void lbm_batch_destroy(lbm_batch *b)
     for (auto &kv : b->graphs) (void)hipGraphExecDestroy(kv.second);
     if (b->capture) (void)hipStreamDestroy(b->capture);
     if (b->h_pin) (void)hipHostFree(b->h_pin);
-    for (int i = 0; i < 2; ++i) {
-        if (b->h_plates[i]) (void)hipHostFree(b->h_plates[i]);
-        if (b->h_tiles[i]) (void)hipHostFree(b->h_tiles[i]);
-        if (b->h_ntiles[i]) (void)hipHostFree(b->h_ntiles[i]);
-        if (b->ev[i]) (void)hipEventDestroy(b->ev[i]);
-    }
+    for (hipEvent_t ev : b->ev)
+        if (ev) (void)hipEventDestroy(ev);
     delete b;
 }
 
