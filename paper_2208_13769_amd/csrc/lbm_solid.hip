@@ -75,6 +75,12 @@ struct lbm_solver {
     Layout L{};
     int cur = 0;  // copy holding the current state
     int jslot = 0, jback = 1;  // buffers of the current j and of the one before it (j extrapolated)
+    // From the first captured step on a graph holds the addresses of these
+    // buffers: where the state lies then depends only on the steps since
+    // set_fields, odd or even, as with one launch per step, and `home` is the
+    // copy (jhome, jhome_back the buffers of j) of an even number of them.
+    bool fixed = false;
+    int home = 0, jhome = 0, jhome_back = 1;
     bool material = false, fields = false;
     double rho0 = 1, lam = 0, mu = 0, tau = 1;
     double body[2] = {0, 0};
@@ -701,9 +707,9 @@ lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0)
     if (!h) return LBM_ERR_ARG;
     if (!u0 || !v0) return fail(h, LBM_ERR_ARG, "u0 or v0 is NULL");
     if (!h->material) return fail(h, LBM_ERR_STATE, "set the material before the fields");
-    h->cur = 0;
-    h->jslot = 0;
-    h->jback = 1;
+    h->cur = h->home;
+    h->jslot = h->jhome;
+    h->jback = h->jhome_back;
     for (auto &w : h->uwb) w[0] = w[1] = 0.0;  // every wall starts undisplaced
     double scale = 1.0;
     bool nonfinite = false;
@@ -712,7 +718,7 @@ lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0)
     if (nonfinite) return fail(h, LBM_ERR_ARG, "initial fields not finite");
     h->f_scale = scale;
     if (h->scheme == LBM_SCHEME_EXTRAP)  // j one step back: j(0) before the first step
-        HIP_TRY(h, hipMemcpyAsync(h->jptr(1), h->jptr(0), 2 * (size_t)h->nx * h->ny * elem_sizes(h->prec).j,
+        HIP_TRY(h, hipMemcpyAsync(h->jbuf(h->jback), h->jbuf(h->jslot), 2 * (size_t)h->nx * h->ny * elem_sizes(h->prec).j,
                                   hipMemcpyDeviceToDevice, h->stream));
     HIP_TRY(h, hipMemsetAsync(h->flag(), 0, sizeof(unsigned), h->stream));
     HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -747,14 +753,23 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     sp.seed = h->seed;
     const int nblocks = h->shape.n_strips * h->shape.n_segs;
     const bool pc = h->scheme == LBM_SCHEME_PC;
-    // Under capture a call leaves the state in the buffers that one launch per
-    // step leaves it in, so that a graph of an even number of steps can be
-    // replayed: an even number of two-step launches, and two buffers of j with a
-    // copy of the older one (the rotation of three comes round after six steps).
+    // A captured call, and from the first one on every call of the handle,
+    // leaves the state in the buffers that one launch per step leaves it in, so
+    // that a graph of an even number of steps can be replayed with even eager
+    // calls and restarts between: an even number of two-step launches, and two
+    // buffers of j with a copy of the older one (the rotation of three comes
+    // round after six steps).
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &capture) != hipSuccess) (void)hipGetLastError();
     const bool captured = capture == hipStreamCaptureStatusActive;
-    const int64_t paired = captured ? nsteps / 4 * 4 : nsteps / 2 * 2;  // steps that two-step launches may take
+    if (captured && !h->fixed) {
+        const bool odd = h->steps & 1;
+        h->fixed = true;
+        h->home = odd ? h->cur ^ 1 : h->cur;
+        h->jhome = odd ? h->jback : h->jslot;
+        h->jhome_back = odd ? h->jslot : h->jback;
+    }
+    const int64_t paired = h->fixed ? nsteps / 4 * 4 : nsteps / 2 * 2;  // steps that two-step launches may take
     auto advance = [&](auto &p) {  // state pointers and index of the next launch
         p.f_in = h->fptr(h->cur);
         p.u_in = h->uptr(h->cur);
@@ -766,7 +781,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
     };
     auto done = [&](int n) {
         h->cur ^= 1;
-        const int next = captured ? h->jback : h->jfree();
+        const int next = h->fixed ? h->jback : h->jfree();
         h->jback = h->jslot;
         h->jslot = next;
         h->steps += n;
@@ -812,7 +827,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
             if (gp.pc != 2) return hipSuccess;
             gp.j_prev = gp.j_out;  // j of the step before, and the third buffer
             void *const third = h->jbuf(h->jfree());
-            if (!captured) {
+            if (!h->fixed) {
                 gp.j_out = third;
                 return hipSuccess;
             }
