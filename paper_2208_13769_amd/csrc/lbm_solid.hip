@@ -922,7 +922,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
         sp2.n_strips = shape.n_strips;
         sp2.n_segs = shape.n_segs;
         const int nb2 = shape.n_strips * shape.n_segs;
-        for (const int64_t end = pairs ? paired : nsteps; k + 2 <= end; k += 2) {
+        for (; k + 2 <= paired; k += 2) {
             advance(sp2);
             HIP_TRY(h, LBM_DISPATCH(h->prec, Kernels<PR>::step2(sp2, shape.block, nb2, h->stream)));
             done(2);

@@ -111,3 +111,11 @@ def _run(nx, ny, precision, scheme, kinds, holes, warm, n, choose=lambda s: None
 ])
 def test_replays_between_even_eager_calls_and_restarts(gpu, nx, ny, precision, scheme, kinds, holes, n):
     _run(nx, ny, precision, scheme, kinds, holes, 2, n)
+
+
+@pytest.mark.parametrize("n", [2, 6])
+@pytest.mark.parametrize("nx,ny,kinds", [(96, 70, FREE), (300, 129, (P_, P_, D_, N_))])
+def test_chosen_two_step_launches_replay_too(gpu, nx, ny, kinds, n):
+    """Two steps per launch set by the caller: a captured call still makes an
+    even number of launches."""
+    _run(nx, ny, "fp64", "pc", kinds, None, 2, n, lambda s: s.set_steps_per_launch(2))
