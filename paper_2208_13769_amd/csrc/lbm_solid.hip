@@ -118,7 +118,13 @@ struct lbm_solver {
         if (fork) (void)hipEventDestroy(fork);
         if (join) (void)hipEventDestroy(join);
         if (aux) (void)hipStreamDestroy(aux);
-        if (pin) (void)hipHostFree(pin);
+        if (!pin) return;
+        // (a handle may go while another stream is being captured, which a free
+        // in any but the relaxed mode would end)
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        (void)hipHostFree(pin);
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
 
     // plates that the fused kernel's walled form cannot run whole
