@@ -1070,7 +1070,8 @@ lbm_status lbm_sample_series(lbm_solver *h, int n, const int *x, const int *y, i
     if (every < 1 && nsteps > 0) return fail(h, LBM_ERR_ARG, "every < 1");
     lbm_status st = lbm_sample(h, n, x, y, out);  // (checks the nodes)
     if (st != LBM_OK) return st;
-    const int64_t m = nsteps > 0 ? (nsteps + every - 1) / every : 0;  // samples after the first
+    // samples after the first (every may be as large as an int64_t)
+    const int64_t m = nsteps > 0 ? nsteps / every + (nsteps % every != 0) : 0;
     const size_t vb = (size_t)17 * n * sizeof(double), ib = align_up((size_t)n * sizeof(int));
     // samples that the page-locked buffer holds at once (the nodes stand in
     // it since the call above)

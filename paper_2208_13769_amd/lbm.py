@@ -422,7 +422,8 @@ class Solver:
         """Advance nsteps, sampling the nodes before the first step and after
         every `every` steps: returns (steps since the call [m], values
         [m][n][17])."""
-        nsteps, every = int(nsteps), int(every)
+        nsteps = int(nsteps)
+        every = int(min(every, max(nsteps, 1)))  # (a longer interval, infinity too: the start and the end)
         vals = lbm_sample_series(self.h, xs, ys, nsteps, every)
         return np.minimum(np.arange(len(vals)) * every, max(nsteps, 0)), vals
 
