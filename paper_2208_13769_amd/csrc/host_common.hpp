@@ -510,9 +510,11 @@ inline hipError_t plate_start(const PlateIO &io, const double *u0, const double 
 }
 
 // Device address of a host array if its `bytes` bytes are page-locked memory
-// that the device can write, else nullptr.
+// that the device can write, else nullptr (also where its doubles do not lie
+// on their own alignment, which a copy takes and a kernel's stores need not).
 inline double *device_address(double *host, size_t bytes)
 {
+    if (reinterpret_cast<uintptr_t>(host) % alignof(double)) return nullptr;
     hipPointerAttribute_t a{}, b{};
     char *last = reinterpret_cast<char *>(host) + bytes - 1;
     if (hipPointerGetAttributes(&a, host) != hipSuccess || hipPointerGetAttributes(&b, last) != hipSuccess) {
