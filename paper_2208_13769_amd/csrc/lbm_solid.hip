@@ -388,12 +388,11 @@ bool plan_pairs(lbm_solver *h)
 constexpr double kBesideSites = 1e7;
 
 // Split of the plate between the fused kernel and windows for launches of
-// `steps` steps; false: the plate leaves the fused kernel no worthwhile share
-// (or the lists no room).
-hipError_t plan_split(lbm_solver *h, int steps)
+// `steps` steps, not used where the plate leaves the fused kernel no worthwhile
+// share (or the lists no room).
+hipError_t build_split(lbm_solver *h, int steps)
 {
     SplitPlan &p = h->split[steps - 1];
-    if (p.built) return hipSuccess;
     p = SplitPlan{};
     p.built = true;
     const int nx = h->nx, ny = h->ny;
@@ -404,7 +403,7 @@ hipError_t plan_split(lbm_solver *h, int steps)
     int mw = 0, mh = 0;
     auto windows = [&](const std::vector<Rect> &rects, int edges, WinGrid &g, int &shape) {
         const bool dev = deviation_storage(h->prec);
-        shape = choose_window(win_class(h->prec), edges, rects, reach, dev, steps, steps).shape;
+        shape = choose_window(win_class(h->prec), edges, rects.data(), (int)rects.size(), reach, dev, steps, steps).shape;
         const int hh = steps * reach + (dev ? 1 : 0);
         mw = win_out(kWinShapes[shape].w, hh);
         mh = win_out(kWinShapes[shape].h, hh);
@@ -466,6 +465,17 @@ hipError_t plan_split(lbm_solver *h, int steps)
     if (extrap) p.inner.list = p.fused_list;
     p.use = true;
     return hipSuccess;
+}
+
+hipError_t plan_split(lbm_solver *h, int steps)
+{
+    if (h->split[steps - 1].built) return hipSuccess;
+    try {
+        return build_split(h, steps);
+    } catch (const std::bad_alloc &) {  // (no exception may leave a C entry)
+        h->split[steps - 1] = SplitPlan{};
+        return hipErrorOutOfMemory;
+    }
 }
 
 }  // namespace
@@ -897,17 +907,17 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
             }
         }
         if (whole_windows || h->split_edges() || gp.pc == 2) {
-            const std::vector<Rect> plate = {Rect{0, 0, h->nx, h->ny}};
+            const Rect plate{0, 0, h->nx, h->ny};
             const int reach = gp.pc ? win_reach<1>() : win_reach<0>();
             const bool dev = deviation_storage(h->prec);
             while (k < nsteps) {
-                const WinChoice c = choose_window(win_class(h->prec), edges, plate, reach, dev, 1,
+                const WinChoice c = choose_window(win_class(h->prec), edges, &plate, 1, reach, dev, 1,
                                                   paired - k >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
                 const int hh = c.steps * reach + (dev ? 1 : 0);
                 WinGrid g{};
                 g.nsteps = c.steps;
                 g.n_regions = 1;
-                g.reg[0] = win_region(plate[0], win_out(kWinShapes[c.shape].w, hh), win_out(kWinShapes[c.shape].h, hh), 0);
+                g.reg[0] = win_region(plate, win_out(kWinShapes[c.shape].w, hh), win_out(kWinShapes[c.shape].h, hh), 0);
                 g.nb = win_blocks(g.reg[0]);
                 const int64_t end = c.steps > 1 ? paired : nsteps;
                 for (; k + c.steps <= end; k += c.steps) {

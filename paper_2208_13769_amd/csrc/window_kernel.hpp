@@ -784,10 +784,10 @@ struct WinChoice {
     int shape, steps;
 };
 
-// The cheapest shape per step for rectangles of a plate, launches of
+// The cheapest shape per step for n_rects rectangles of a plate, launches of
 // min_steps to max_steps steps (reach rings each, one more with deviation
-// storage).
-inline WinChoice choose_window(int cls, int edges, const std::vector<Rect> &rects, int reach, bool dev, int min_steps,
+// storage). Called for each lbm_step: no allocation.
+inline WinChoice choose_window(int cls, int edges, const Rect *rects, int n_rects, int reach, bool dev, int min_steps,
                                int max_steps)
 {
     WinChoice best{0, min_steps};
@@ -798,7 +798,7 @@ inline WinChoice choose_window(int cls, int edges, const std::vector<Rect> &rect
         const int mw = win_out(kWinShapes[c.shape].w, h), mh = win_out(kWinShapes[c.shape].h, h);
         if (!mw || !mh) continue;
         double nb = 0;
-        for (const Rect &r : rects) nb += win_blocks(win_region(r, mw, mh, 0));
+        for (int k = 0; k < n_rects; ++k) nb += win_blocks(win_region(rects[k], mw, mh, 0));
         const double per_cu = nb / 256.0, full = per_cu < 2.0   ? 0.5 * (per_cu + std::ceil(per_cu))
                                                        : per_cu < 4.0 ? std::ceil(per_cu)
                                                                       : per_cu;

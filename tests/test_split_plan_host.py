@@ -13,7 +13,22 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 SOURCE = r"""
+#include <cstdlib>
 #include "split_plan.hpp"
+static long news = 0;
+void *operator new(size_t n) { ++news; return std::malloc(n); }
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+// shape and steps chosen for n rectangles of w x h nodes, and the host allocations made for it
+extern "C" long choose(int cls, int edges, int w, int h, int n, int *shape, int *steps)
+{
+    std::vector<lbm::Rect> r(n, lbm::Rect{0, 0, w, h});
+    const long before = news;
+    const lbm::WinChoice c = lbm::choose_window(cls, edges, r.data(), n, 5, cls == 3, 1, lbm::kWinMaxSteps);
+    *shape = c.shape;
+    *steps = c.steps;
+    return news - before;
+}
 // tiles (x, columns, y0, y1) and rectangles (x, y, w, h), at most cap each
 extern "C" void plan_mask(int nx, int ny, int perx, int pery, int reach, int align, const unsigned char *mask,
                           int strip_w, int slots, int cap, int *tiles, int *n_tiles, int *rects, int *n_rects)
@@ -116,3 +131,13 @@ def test_a_plan_takes_time_in_proportion_to_the_plate(lib):
         t.append(min(_plan(lib, mask, True, True, 10, 16, 224, 512)[2] for _ in range(3)))
     print(f"plans of 256 x 16384 and 256 x 131072: {t[0] * 1e3:.1f} and {t[1] * 1e3:.1f} ms")
     assert t[1] < 24 * t[0]
+
+
+@pytest.mark.parametrize("cls", range(4))
+@pytest.mark.parametrize("edges", range(3))
+def test_choosing_a_window_allocates_nothing(lib, cls, edges):
+    """It is part of every lbm_step of a small plate."""
+    for w, h in ((5, 5), (64, 64), (300, 97), (1021, 777)):
+        shape, steps = ctypes.c_int(-1), ctypes.c_int(-1)
+        assert lib.choose(cls, edges, w, h, 1, ctypes.byref(shape), ctypes.byref(steps)) == 0
+        assert 0 <= shape.value < 6 and steps.value in (1, 2)
