@@ -66,6 +66,7 @@ static __device__ __align__(256) double scratch[kNoAllocDiagDoubles];
 struct lbm_solver {
     int nx = 0, ny = 0;
     int device = 0;  // the device current at lbm_create
+    int cus = 256;   // its compute units
     double dx = 1.0;
     lbm_precision prec = LBM_FP64;
     lbm_scheme scheme = LBM_SCHEME_PC;
@@ -403,7 +404,7 @@ hipError_t build_split(lbm_solver *h, int steps)
     int mw = 0, mh = 0;
     auto windows = [&](const std::vector<Rect> &rects, int edges, WinGrid &g, int &shape) {
         const bool dev = deviation_storage(h->prec);
-        shape = choose_window(win_class(h->prec), edges, rects.data(), (int)rects.size(), reach, dev, steps, steps).shape;
+        shape = choose_window(h->cus, win_class(h->prec), edges, rects.data(), (int)rects.size(), reach, dev, steps, steps).shape;
         const int hh = steps * reach + (dev ? 1 : 0);
         mw = win_out(kWinShapes[shape].w, hh);
         mh = win_out(kWinShapes[shape].h, hh);
@@ -524,6 +525,8 @@ lbm_status lbm_create(int nx, int ny, double dx, lbm_precision p, lbm_scheme s, 
     h->stream = static_cast<hipStream_t>(hip_stream);
     h->L = L;
     if (hipGetDevice(&h->device) != hipSuccess) h->device = 0;
+    if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || h->cus < 1)
+        h->cus = 256;
     plan_launch(h);
     *out = h;
     return LBM_OK;
@@ -911,7 +914,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
             const int reach = gp.pc ? win_reach<1>() : win_reach<0>();
             const bool dev = deviation_storage(h->prec);
             while (k < nsteps) {
-                const WinChoice c = choose_window(win_class(h->prec), edges, &plate, 1, reach, dev, 1,
+                const WinChoice c = choose_window(h->cus, win_class(h->prec), edges, &plate, 1, reach, dev, 1,
                                                   paired - k >= 2 && gp.pc != 2 ? kWinMaxSteps : 1);
                 const int hh = c.steps * reach + (dev ? 1 : 0);
                 WinGrid g{};

@@ -786,9 +786,10 @@ struct WinChoice {
 
 // The cheapest shape per step for n_rects rectangles of a plate, launches of
 // min_steps to max_steps steps (reach rings each, one more with deviation
-// storage). Called for each lbm_step: no allocation.
-inline WinChoice choose_window(int cls, int edges, const Rect *rects, int n_rects, int reach, bool dev, int min_steps,
-                               int max_steps)
+// storage) on a device of `cus` compute units. Called for each lbm_step: no
+// allocation.
+inline WinChoice choose_window(int cus, int cls, int edges, const Rect *rects, int n_rects, int reach, bool dev,
+                               int min_steps, int max_steps)
 {
     WinChoice best{0, min_steps};
     double best_t = 1e300;
@@ -799,7 +800,7 @@ inline WinChoice choose_window(int cls, int edges, const Rect *rects, int n_rect
         if (!mw || !mh) continue;
         double nb = 0;
         for (int k = 0; k < n_rects; ++k) nb += win_blocks(win_region(rects[k], mw, mh, 0));
-        const double per_cu = nb / 256.0, full = per_cu < 2.0   ? 0.5 * (per_cu + std::ceil(per_cu))
+        const double per_cu = nb / cus, full = per_cu < 2.0   ? 0.5 * (per_cu + std::ceil(per_cu))
                                                        : per_cu < 4.0 ? std::ceil(per_cu)
                                                                       : per_cu;
         const double one = c.lat + (c.lat1 - c.lat) * std::min(1.0, per_cu);

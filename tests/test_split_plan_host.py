@@ -20,11 +20,11 @@ void *operator new(size_t n) { ++news; return std::malloc(n); }
 void operator delete(void *p) noexcept { std::free(p); }
 void operator delete(void *p, size_t) noexcept { std::free(p); }
 // shape and steps chosen for n rectangles of w x h nodes, and the host allocations made for it
-extern "C" long choose(int cls, int edges, int w, int h, int n, int *shape, int *steps)
+extern "C" long choose(int cus, int cls, int edges, int w, int h, int n, int *shape, int *steps)
 {
     std::vector<lbm::Rect> r(n, lbm::Rect{0, 0, w, h});
     const long before = news;
-    const lbm::WinChoice c = lbm::choose_window(cls, edges, r.data(), n, 5, cls == 3, 1, lbm::kWinMaxSteps);
+    const lbm::WinChoice c = lbm::choose_window(cus, cls, edges, r.data(), n, 5, cls == 3, 1, lbm::kWinMaxSteps);
     *shape = c.shape;
     *steps = c.steps;
     return news - before;
@@ -139,5 +139,22 @@ def test_choosing_a_window_allocates_nothing(lib, cls, edges):
     """It is part of every lbm_step of a small plate."""
     for w, h in ((5, 5), (64, 64), (300, 97), (1021, 777)):
         shape, steps = ctypes.c_int(-1), ctypes.c_int(-1)
-        assert lib.choose(cls, edges, w, h, 1, ctypes.byref(shape), ctypes.byref(steps)) == 0
+        assert lib.choose(256, cls, edges, w, h, 1, ctypes.byref(shape), ctypes.byref(steps)) == 0
         assert 0 <= shape.value < 6 and steps.value in (1, 2)
+
+
+@pytest.mark.parametrize("edges", range(3))
+def test_windows_are_priced_by_the_device_s_compute_units(lib, edges):
+    """An eighth of the windows on an eighth of the compute units: the same
+    choice."""
+    def choice(cus, w, h, n):
+        shape, steps = ctypes.c_int(), ctypes.c_int()
+        lib.choose(cus, 1, edges, w, h, n, ctypes.byref(shape), ctypes.byref(steps))
+        return shape.value, steps.value
+
+    seen = set()
+    for side in (20, 64, 100, 150, 220, 300, 500):
+        want = choice(256, side, side, 8)
+        seen.add(want)
+        assert choice(32, side, side, 1) == want
+    assert len(seen) > 1  # (the size matters)
