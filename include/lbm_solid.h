@@ -244,6 +244,17 @@ lbm_status lbm_resident_blocks(const lbm_solver *h, int block, int steps_per_lau
  * workspace beyond what the plate's edges, mask and scheme already need. */
 lbm_status lbm_set_general_path(lbm_solver *h, int on);
 
+/* Back to the library's own plan, as after lbm_create: takes back
+ * lbm_set_general_path, lbm_set_tiling and lbm_set_steps_per_launch. Between
+ * y walls a large plate's own plan (the fused kernel's periodic form clear of
+ * the walls, two steps per launch, windows along them) is none of the shapes
+ * those calls choose. */
+lbm_status lbm_set_default_plan(lbm_solver *h);
+
+/* What a plan depends on besides size, precision and scheme: the rule of each
+ * edge (lbm_bc, lbm_edge order) and whether a mask is set. */
+lbm_status lbm_get_edges(const lbm_solver *h, int kinds[4], int *has_mask);
+
 /* Holes in the plate (the plate with a hole of Sec. 7.2). solid: host array
  * [ny][nx], nonzero for a material node, 0 for a node in a hole; NULL
  * removes the mask. A link from a material node into a hole crosses a

@@ -2,18 +2,20 @@
 
 The step's results do not depend on how it is launched, only its speed does:
 the fused step kernel's shape (threads per block = columns per strip + halo,
-row segments per strip, one or two steps per launch), or the general step
-(2D windows whose stages run in parallel, the faster one on small plates). For
-a plate size, precision and scheme the tuner times a short run of each
-candidate with HIP events on the solver's stream, times the fastest few
+row segments per strip, one or two steps per launch), the general step
+(2D windows whose stages run in parallel, the faster one on small plates), or
+the library's own plan where no such choice expresses it (between y walls: the
+fused kernel and windows together). For a plate size, precision, scheme and
+kind of edges the tuner times a short run of each candidate with HIP events on the solver's stream, times the fastest few
 again over longer runs, and keeps the fastest of those.
 Results are cached in a JSON file (``$LBM_AUTOTUNE_CACHE``, default
 ``~/.cache/lbm_solid/autotune.json``) keyed by device name and problem.
 
 Tuning advances the solver's state: call ``set_fields`` again afterwards.
 ``best_tiling`` returns (block, segments, steps per launch), with
-``GENERAL`` = (0, 0, 1) standing for the general step; ``apply_tiling`` sets
-either on a solver.
+``GENERAL`` = (0, 0, 1) standing for the general step and ``DEFAULT`` =
+(0, 0, 0) for the library's own plan; ``apply_tiling`` sets any of them on a
+solver.
 """
 from __future__ import annotations
 
@@ -22,6 +24,8 @@ import os
 
 HALO = {"pc": 5, "explicit": 3}
 GENERAL = (0, 0, 1)  # the general step in place of a fused-kernel shape
+DEFAULT = (0, 0, 0)  # the library's own plan
+PERIODIC = 0  # an edge's rule (the others are walls)
 
 
 def _cache_path() -> str:
@@ -97,6 +101,12 @@ def candidates(solver, nx: int, ny: int, precision: str, scheme: str):
                 if n_str * segs <= resident and segs not in seen:
                     seen.add(segs)
                     out.append((block, segs, spl))
+    # The shapes above and the general step are all that a periodic plate's own
+    # plan takes, and with x walls or a mask nothing but that plan runs. Between y
+    # walls it is a candidate of its own.
+    kinds, mask = solver.edges() if hasattr(solver, "edges") else ((PERIODIC,) * 4, False)
+    if kinds[2] != PERIODIC and kinds[0] == PERIODIC and not mask:
+        out.append(DEFAULT)
     out.append(GENERAL)
     return out
 
@@ -104,6 +114,9 @@ def candidates(solver, nx: int, ny: int, precision: str, scheme: str):
 def apply_tiling(solver, tiling) -> None:
     """Run the solver's steps with a candidate of ``candidates``."""
     block, segs, spl = tiling
+    if tuple(tiling) == DEFAULT:
+        solver.set_default_plan()
+        return
     if tuple(tiling) == GENERAL:
         solver.set_general_path(True)
         return

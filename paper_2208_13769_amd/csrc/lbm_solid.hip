@@ -93,7 +93,7 @@ struct lbm_solver {
     double uwb[4][2] = {};
     double f_scale = 1.0;
     int64_t steps = 0;
-    Shape shape{};
+    Shape shape{}, created_shape{};  // of the fused kernel now, and as lbm_create planned it
     int spl = 1;  // time steps per launch (1, or 2 with the predictor-corrector)
     int sr = 0;   // stochastic rounding of 16-bit populations
     unsigned long long seed = 0;
@@ -528,6 +528,7 @@ lbm_status lbm_create(int nx, int ny, double dx, lbm_precision p, lbm_scheme s, 
     if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess || h->cus < 1)
         h->cus = 256;
     plan_launch(h);
+    h->created_shape = h->shape;
     *out = h;
     return LBM_OK;
 }
@@ -684,6 +685,24 @@ lbm_status lbm_set_general_path(lbm_solver *h, int on)
     // workspace; the general step of any other plate needs no more)
     h->force_general = on != 0;
     h->fused_set = !on;
+    return LBM_OK;
+}
+
+lbm_status lbm_set_default_plan(lbm_solver *h)
+{
+    if (!h) return LBM_ERR_ARG;
+    h->force_general = false;
+    h->fused_set = false;
+    h->spl = 1;
+    h->shape = h->created_shape;
+    return LBM_OK;
+}
+
+lbm_status lbm_get_edges(const lbm_solver *h, int kinds[4], int *has_mask)
+{
+    if (!h || !kinds || !has_mask) return LBM_ERR_ARG;
+    for (int e = 0; e < 4; ++e) kinds[e] = h->bc[e];
+    *has_mask = h->has_mask;
     return LBM_OK;
 }
 

@@ -40,6 +40,7 @@ EXPORTED = [
     "lbm_resident_blocks", "lbm_set_rounding", "lbm_read_derived", "lbm_sample", "lbm_sample_series",
     "lbm_batch_read_derived",
     "lbm_batch_sample", "lbm_workspace_bytes_walled", "lbm_set_general_path", "lbm_set_mask",
+    "lbm_set_default_plan", "lbm_get_edges",
     "lbm_batch_plate_bytes", "lbm_batch_plate_tiles", "lbm_batch_workspace_bytes", "lbm_batch_create",
     "lbm_batch_add", "lbm_batch_step", "lbm_batch_query", "lbm_batch_read", "lbm_batch_retire", "lbm_batch_info",
     "lbm_batch_destroy", "lbm_batch_last_error", "lbm_batch_set_steps_per_launch",
@@ -85,6 +86,10 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.lbm_workspace_bytes_walled.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int]
     lib.lbm_set_general_path.restype = ctypes.c_int
     lib.lbm_set_general_path.argtypes = [vp, ctypes.c_int]
+    lib.lbm_set_default_plan.restype = ctypes.c_int
+    lib.lbm_set_default_plan.argtypes = [vp]
+    lib.lbm_get_edges.restype = ctypes.c_int
+    lib.lbm_get_edges.argtypes = [vp, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
     lib.lbm_set_mask.restype = ctypes.c_int
     lib.lbm_set_mask.argtypes = [vp, vp]
     lib.lbm_create.restype = ctypes.c_int
@@ -158,6 +163,17 @@ def lbm_workspace_bytes_walled(nx: int, ny: int, precision: int) -> int:
 
 def lbm_set_general_path(h, on: bool):
     _check(load_library().lbm_set_general_path(h, int(bool(on))), h)
+
+
+def lbm_set_default_plan(h):
+    _check(load_library().lbm_set_default_plan(h), h)
+
+
+def lbm_get_edges(h):
+    """((rule of each edge), whether a mask is set)."""
+    kinds, mask = (ctypes.c_int * 4)(), ctypes.c_int()
+    _check(load_library().lbm_get_edges(h, kinds, ctypes.byref(mask)), h)
+    return tuple(kinds), bool(mask.value)
 
 
 def lbm_set_mask(h, solid):
@@ -367,6 +383,14 @@ class Solver:
 
     def set_general_path(self, on: bool):
         lbm_set_general_path(self.h, on)
+
+    def set_default_plan(self):
+        """The library's own plan again, whatever set_general_path, set_tiling
+        and set_steps_per_launch chose."""
+        lbm_set_default_plan(self.h)
+
+    def edges(self):
+        return lbm_get_edges(self.h)
 
     def set_mask(self, solid):
         """solid: [ny][nx] array, nonzero for material, 0 for holes; None removes it."""
