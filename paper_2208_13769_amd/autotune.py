@@ -9,7 +9,8 @@ fused kernel and windows together). For a plate size, precision, scheme and
 kind of edges the tuner times a short run of each candidate with HIP events on the solver's stream, times the fastest few
 again over longer runs, and keeps the fastest of those.
 Results are cached in a JSON file (``$LBM_AUTOTUNE_CACHE``, default
-``~/.cache/lbm_solid/autotune.json``) keyed by device name and problem.
+``~/.cache/lbm_solid/autotune.json``) keyed by device name, problem and the
+version of what the choices stand for.
 
 Tuning advances the solver's state: call ``set_fields`` again afterwards.
 ``best_tiling`` returns (block, segments, steps per launch), with
@@ -171,10 +172,21 @@ def tune(solver, nx: int, ny: int, precision: str, scheme: str, window_ms: float
     return best, best_ms, table
 
 
+# Raised whenever a kernel or plan that a cached choice stands for changes.
+CACHE_VERSION = 8
+
+
+def cache_key(device: str, nx: int, ny: int, precision: str, scheme: str, kinds, mask: bool) -> str:
+    """Edges and mask decide which kernels a plate runs and which shapes it
+    may: a two-step shape of 512 threads fits between periodic edges only."""
+    edges = "".join(str(int(k)) for k in kinds) + ("m" if mask else "")
+    return f"{device}|{nx}x{ny}|{precision}|{scheme}|{edges}|v{CACHE_VERSION}"
+
+
 def best_tiling(solver, nx: int, ny: int, precision: str, scheme: str):
     import torch
 
-    key = f"{torch.cuda.get_device_name(solver.device)}|{nx}x{ny}|{precision}|{scheme}|v7"
+    key = cache_key(torch.cuda.get_device_name(solver.device), nx, ny, precision, scheme, *solver.edges())
     cache = _load_cache()
     if key in cache:
         return tuple(cache[key]["tiling"])
