@@ -141,16 +141,24 @@ struct lbm_solver {
     // windows / that: periodic FP64 700^2 31.9 / 31.8, FP32 1000^2 27.6 / 27.1,
     // FP32_U64 1400^2 53 / 48, FP16 1400^2 65 / 61; y walls FP64 700^2 34 / 39,
     // 1000^2 70 / 49, FP32 1000^2 33.8 / 34.1, FP32_U64 39 / 43, FP16 1400^2 73
-    // / 71; four walls FP64 500^2 33 / 38, 700^2 51 / 47, FP32 1000^2 38 / 37,
-    // FP32_U64 49 / 47, FP16 51 / 50. Narrow plates go by their sites too.
+    // / 71; four walls, and with a hole, FP64 700^2 43 / 42, 46 / 46, FP32 900^2 32
+    // / 30, 35 / 38, 1000^2 42 / 31, 48 / 39, FP32_U64 950^2 43 / 40, 48 / 48, FP16
+    // 950^2 51 / 51, 57 / 52. The explicit scheme's windows lose three rings a step
+    // where these lose five: four walls 1000^2 FP64 47 / 57, FP32 24 / 32, FP32_U64
+    // 27 / 36, FP16 31 / 35; y walls FP64 1000^2 39 / 52, 1700^2 128 / 148. Narrow
+    // plates go by their sites too.
     bool windows() const
     {
         if (scheme == LBM_SCHEME_EXTRAP) return !walls() || (double)nx * ny <= 3e5;
         if (force_general && !split_edges()) return true;
         if (fused_set && !split_edges()) return false;
-        static const double limit[3][4] = {{5e5, 1.0e6, 1.2e6, 1.2e6},   // periodic: FP64, FP32, FP32_U64, 16-bit
-                                           {6e5, 1.0e6, 1.1e6, 1.8e6},   // y walls
-                                           {5e5, 1.0e6, 1.0e6, 1.0e6}};  // x walls or holes
+        static const double limits[2][3][4] = {{{5e5, 1.0e6, 1.2e6, 1.2e6},     // periodic: FP64, FP32, FP32_U64, 16-bit
+                                                {6e5, 1.0e6, 1.1e6, 1.8e6},     // y walls
+                                                {5e5, 8.5e5, 9.0e5, 8.5e5}},    // x walls or holes
+                                               {{5e5, 1.0e6, 1.2e6, 1.2e6},     // the explicit scheme
+                                                {2.9e6, 1.0e6, 1.1e6, 1.8e6},
+                                                {5e5, 1.0e6, 1.0e6, 1.0e6}}};
+        const auto &limit = limits[scheme == LBM_SCHEME_EXPLICIT];
         const int kind = split_edges() ? 2 : bc[LBM_EDGE_YMIN] != LBM_BC_PERIODIC ? 1 : 0;
         return (double)nx * ny <= limit[kind][win_class(prec)];
     }
