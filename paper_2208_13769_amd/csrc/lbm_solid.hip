@@ -396,6 +396,29 @@ bool plan_pairs(lbm_solver *h)
 // 152 / 155; FP32_U64 271 / 267, 97 / 102; FP16 364 / 358, 122 / 132).
 constexpr double kBesideSites = 1e7;
 
+// Blocks of a plan's fused share: all that the device holds at once, but with the
+// explicit scheme in the 32-bit forms two per compute unit of the five (four)
+// that fit: longer segments recompute fewer halo rows (us per step, all / two:
+// with a hole FP32 2500^2 182 / 167, 4096^2 389 / 366, FP32_U64 193 / 185, 425 /
+// 411; four walls 4096^2 424 / 405, 469 / 454). FP64 holds two, the 16-bit forms
+// three (1800^2 81, with two 84). In FP64 a plate of 4.4 to 7 million
+// sites with holes runs 0.9 per compute unit, beside windows that take a last
+// strip of 16 columns too (2100^2 223 / 216, 2400^2 257 / 250, 2500^2 303 / 286,
+// 2600^2 318 / 311; outside, 2000^2 181 / 194, 2800^2 346 / 351).
+bool lean_share(const lbm_solver *h)
+{
+    const double sites = (double)h->nx * h->ny;
+    return h->scheme == LBM_SCHEME_EXPLICIT && h->prec == LBM_FP64 && h->has_mask && sites >= 4.4e6 && sites < 7e6;
+}
+
+int share_blocks(const lbm_solver *h, int block, int steps)
+{
+    const int all = resident_blocks(h, block, steps, 0);
+    if (lean_share(h)) return std::min(all, (int)(0.9 * h->cus));
+    const bool two = h->scheme == LBM_SCHEME_EXPLICIT && !deviation_storage(h->prec);
+    return two ? std::min(all, 2 * h->cus) : all;
+}
+
 // Split of the plate between the fused kernel and windows for launches of
 // `steps` steps, not used where the plate leaves the fused kernel no worthwhile
 // share (or the lists no room).
@@ -409,6 +432,7 @@ hipError_t build_split(lbm_solver *h, int steps)
                        stencil_halo(h->prec, h->scheme, steps), h->prec == LBM_FP64 ? 16 : 32};
     const int reach = h->scheme == LBM_SCHEME_EXPLICIT ? win_reach<0>() : win_reach<1>();
     const bool extrap = h->scheme == LBM_SCHEME_EXTRAP;
+    p.beside = h->split_edges() && ((double)nx * ny >= kBesideSites || lean_share(h));
     int mw = 0, mh = 0;
     auto windows = [&](const std::vector<Rect> &rects, int edges, WinGrid &g, int &shape) {
         const bool dev = deviation_storage(h->prec);
@@ -426,7 +450,7 @@ hipError_t build_split(lbm_solver *h, int steps)
         p.shape = make_shape(nx, ny, h->prec, h->scheme, block, 1, steps);
         p.box = box;
         p.shape.n_strips = (box.w + p.shape.strip_w - 1) / p.shape.strip_w;
-        p.shape.n_segs = std::max(1, std::min(resident_blocks(h, block, steps, 0) / p.shape.n_strips, box.h / 8));
+        p.shape.n_segs = std::max(1, std::min(share_blocks(h, block, steps) / p.shape.n_strips, box.h / 8));
         auto regions = [&](const std::vector<Rect> &rects, WinGrid &g) {
             for (const Rect &r : rects) {
                 g.reg[g.n_regions] = win_region(r, mw, mh, g.nb);
@@ -446,8 +470,8 @@ hipError_t build_split(lbm_solver *h, int steps)
     p.shape = make_shape(nx, ny, h->prec, h->scheme, 256, 1, steps);
     std::vector<int4> list;
     std::vector<Rect> rects;
-    split_mask(e, h->mask_host.data(), extrap ? nx : p.shape.strip_w, extrap ? 1 : resident_blocks(h, 256, steps, 0),
-               list, rects);
+    split_mask(e, h->mask_host.data(), extrap ? nx : p.shape.strip_w, lean_share(h) ? 32 : 0,
+               extrap ? 1 : share_blocks(h, 256, steps), list, rects);
     if (list.empty()) return hipSuccess;
     if (extrap) {
         std::vector<Rect> clear;
@@ -906,7 +930,7 @@ lbm_status lbm_step(lbm_solver *h, int64_t nsteps)
                 fp.y_lo = p.box.y;
                 fp.y_end = p.box.y + p.box.h;
                 const int nb = p.shape.n_strips * p.shape.n_segs;
-                const bool beside = h->split_edges() && (double)h->nx * h->ny >= kBesideSites;
+                const bool beside = p.beside;
                 if (beside && !h->aux) {
                     HIP_TRY(h, hipStreamCreateWithFlags(&h->aux, hipStreamNonBlocking));
                     HIP_TRY(h, hipEventCreateWithFlags(&h->fork, hipEventDisableTiming));

@@ -24,6 +24,7 @@ constexpr int kSplitMinCols = 96, kSplitMinRows = 32;
 
 struct SplitPlan {
     bool built = false, use = false;
+    bool beside = false;  // the windows run on the handle's second stream
     Shape shape{};  // of the fused share
     Rect box{};     // its part of the plate (no list)
     const int4 *fused_list = nullptr;  // or its tiles, x, columns, y0, y1
@@ -79,9 +80,10 @@ inline std::vector<Rect> split_frame(const SplitEdges &e, const Rect &b)
 // `tiles`), the rest of the plate rectangles for windows. Neighbouring runs
 // are merged, at the cost of the columns clear in only one of them, where the
 // rows a fused tile marches before its first output cost more. Tiles are cut
-// to at most `slots`, one wave of resident blocks, where strips allow.
-inline void split_mask(const SplitEdges &e, const unsigned char *mask, int strip_w, int slots, std::vector<int4> &tiles,
-                       std::vector<Rect> &rects)
+// to at most `slots`, one wave of blocks, where strips allow. A last strip of
+// fewer than min_strip columns is left to the windows.
+inline void split_mask(const SplitEdges &e, const unsigned char *mask, int strip_w, int min_strip, int slots,
+                       std::vector<int4> &tiles, std::vector<Rect> &rects)
 {
     constexpr int RH = 4;
     const int CW = e.align;
@@ -199,7 +201,13 @@ inline void split_mask(const SplitEdges &e, const unsigned char *mask, int strip
             if (x1 - x0 < kSplitMinCols || r.y1 - r.y0 < kSplitMinRows) {
                 for (int k = c; k < d; ++k) r.dirty[k] = 1;
             } else {
-                for (int x = x0; x < x1; x += strip_w) strips.push_back(Strip{x, std::min(strip_w, x1 - x), r.y0, r.y1});
+                for (int x = x0; x < x1; x += strip_w) {
+                    if (x > x0 && x1 - x < min_strip) {
+                        for (int k = x / CW; k < d; ++k) r.dirty[k] = 1;
+                        break;
+                    }
+                    strips.push_back(Strip{x, std::min(strip_w, x1 - x), r.y0, r.y1});
+                }
             }
             c = d;
         }

@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (1187, 949, "fp32", "explicit", (N_, D_, D_, N_), None, 3),
     (1187, 949, "fp16", "pc", (N_, N_, N_, N_), "round", 5),
     (3301, 3067, "fp32", "pc", (N_, N_, D_, N_), "round", 4),    # windows on the second stream
+    (2111, 2099, "fp64", "explicit", (N_, N_, D_, N_), "round", 3),  # windows beside the share, a thin strip theirs
 ])
 def test_split_plate_velocity(gpu, nx, ny, precision, scheme, kinds, holes, n):
     m = _mask(nx, ny, kinds, holes)

@@ -31,12 +31,12 @@ extern "C" long choose(int cus, int cls, int edges, int w, int h, int n, int *sh
 }
 // tiles (x, columns, y0, y1) and rectangles (x, y, w, h), at most cap each
 extern "C" void plan_mask(int nx, int ny, int perx, int pery, int reach, int align, const unsigned char *mask,
-                          int strip_w, int slots, int cap, int *tiles, int *n_tiles, int *rects, int *n_rects)
+                          int strip_w, int min_strip, int slots, int cap, int *tiles, int *n_tiles, int *rects, int *n_rects)
 {
     const lbm::SplitEdges e{nx, ny, perx != 0, pery != 0, reach, align};
     std::vector<int4> t;
     std::vector<lbm::Rect> r;
-    lbm::split_mask(e, mask, strip_w, slots, t, r);
+    lbm::split_mask(e, mask, strip_w, min_strip, slots, t, r);
     *n_tiles = (int)t.size();
     *n_rects = (int)r.size();
     for (int k = 0; k < std::min(cap, *n_tiles); ++k) {
@@ -62,14 +62,14 @@ def lib(tmp_path_factory):
     return ctypes.CDLL(str(so))
 
 
-def _plan(lib, mask, perx, pery, reach, align, strip_w, slots):
+def _plan(lib, mask, perx, pery, reach, align, strip_w, slots, min_strip=0):
     ny, nx = mask.shape
     cap = mask.size // 8 + 4096
     tiles, rects = np.zeros((cap, 4), np.int32), np.zeros((cap, 4), np.int32)
     nt, nr = ctypes.c_int(), ctypes.c_int()
     ptr = lambda a: a.ctypes.data_as(ctypes.c_void_p)
     t0 = time.perf_counter()
-    lib.plan_mask(nx, ny, int(perx), int(pery), reach, align, ptr(mask), strip_w, slots, cap, ptr(tiles),
+    lib.plan_mask(nx, ny, int(perx), int(pery), reach, align, ptr(mask), strip_w, min_strip, slots, cap, ptr(tiles),
                   ctypes.byref(nt), ptr(rects), ctypes.byref(nr))
     dt = time.perf_counter() - t0
     assert nt.value <= cap and nr.value <= cap
@@ -104,7 +104,8 @@ def test_plans_cover_the_plate_clear_of_walls_and_holes(lib, seed):
     reach, align = int(rng.choice([3, 5, 6, 10])), int(rng.choice([16, 32]))
     strip_w, slots = int(rng.choice([64, 96, 224])), int(rng.choice([1, 16, 512]))
     mask = _scattered(nx, ny, rng, int(rng.integers(1, 12)), 40)
-    tiles, rects, _ = _plan(lib, mask, perx, pery, reach, align, strip_w, slots)
+    min_strip = 32 if seed % 3 == 0 else 0
+    tiles, rects, _ = _plan(lib, mask, perx, pery, reach, align, strip_w, slots, min_strip)
     seen = np.zeros((ny, nx), np.int32)
     fused = np.zeros((ny, nx), bool)
     for x, w, y0, y1 in tiles:
