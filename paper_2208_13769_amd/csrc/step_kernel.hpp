@@ -823,7 +823,9 @@ __device__ __forceinline__ int row_load(int r, int ny)
 // instructions, which a wave issues in order with its vector ones). us per step
 // before / with it: FP32_U64 2500^2 126.7 / 119.5, 4096^2 262.6 / 257.9; FP64
 // 1400^2 77.2 / 75.1; 16-bit forms, bound by their vector instructions, as
-// before.
+// before. Single FP64 plates of two steps per launch on 256 threads (one wave
+// per SIMD, 244 accumulation registers) keep the modulo: 4096^2 414.1, with
+// counters 419.8, 2500^2 246.2 / 249.2.
 struct RowCounter {
     uint32_t off, nx, total;
     __device__ __forceinline__ RowCounter(int r, int nx_, int ny)
@@ -1047,7 +1049,7 @@ constexpr int step2_unroll()
     return (sizeof(typename PR::TU) == 8 && sizeof(typename PR::TC) == 4) ? 1 : 4;
 }
 
-template <class PR, int BLOCK, bool WALLED>
+template <class PR, int BLOCK, bool WALLED, bool COUNT = true>
 __device__ __forceinline__ void step2_tile(const StepParams &p, const TileGeom &g,
                                            TileLds<PR, BLOCK, true, WALLED> &lds1,
                                            TileLds<PR, BLOCK, true, WALLED> &lds2)
@@ -1084,10 +1086,13 @@ __device__ __forceinline__ void step2_tile(const StepParams &p, const TileGeom &
     const int Rstart = g.y0 - 10;
     RowCounter cA(Rstart, nx, ny), cC(Rstart - 2, nx, ny), cD(Rstart - 10, nx, ny), cF(Rstart - 12, nx, ny);
     auto load_at = [&](const RowCounter &c, int r) {
-        return row_offset((WALLED ? (uint32_t)row_load<WALLED>(r, ny) * (uint32_t)nx : c.off) + (uint32_t)g.gx);
+        return row_offset((WALLED || !COUNT ? (uint32_t)row_load<WALLED>(r, ny) * (uint32_t)nx : c.off) + (uint32_t)g.gx);
     };
     auto store_at = [&](const RowCounter &c, int r) {
-        return row_offset((WALLED ? (uint32_t)r * (uint32_t)nx : c.off) + (uint32_t)g.gx);
+        return row_offset((WALLED   ? (uint32_t)r * (uint32_t)nx
+                           : COUNT ? c.off
+                                   : (uint32_t)row_load<false>(r, ny) * (uint32_t)nx) +
+                          (uint32_t)g.gx);
     };
 
     auto row = [&](auto phase, const int R, const int b) {
@@ -1207,7 +1212,7 @@ __global__ void __launch_bounds__(BLOCK) step2_list_kernel(const StepParams p, c
     const int xcd = bid & 7, loc = bid >> 3;
     const int logical = xcd * xq + min(xcd, xr) + loc;
     __shared__ TileLds<PR, BLOCK, true, false> lds[2];
-    step2_tile<PR, BLOCK, false>(p, tile_geom(p, list[logical]), lds[0], lds[1]);
+    step2_tile<PR, BLOCK, false, !(BLOCK == 256 && sizeof(typename PR::TC) == 8)>(p, tile_geom(p, list[logical]), lds[0], lds[1]);
 }
 
 // Two steps per launch, one block per tile (same tile order as step_kernel).
@@ -1222,7 +1227,12 @@ __global__ void __launch_bounds__(BLOCK) step2_kernel(const StepParams p)
     const int seg = logical / p.n_strips;
     const int strip = logical - seg * p.n_strips;
     __shared__ TileLds<PR, BLOCK, true, WALLED> lds[2];
-    step2_tile<PR, BLOCK, WALLED>(p, tile_geom(p, strip, seg), lds[0], lds[1]);
+    TileGeom g = tile_geom(p, strip, seg);
+    if constexpr (WALLED) {  // (the whole height)
+        g.y0 = (int)((long long)seg * p.ny / p.n_segs);
+        g.y1 = (int)((long long)(seg + 1) * p.ny / p.n_segs);
+    }
+    step2_tile<PR, BLOCK, WALLED, !(BLOCK == 256 && sizeof(typename PR::TC) == 8)>(p, g, lds[0], lds[1]);
 }
 
 }  // namespace lbm
