@@ -147,11 +147,22 @@ inline void fill_physics(StepParams &sp, const Units &U, double tau_over_dt, con
 
 template <class PR>
 struct Kernels {
+    // The walled FP32 predictor-corrector step takes 129 registers, one more
+    // than four waves per SIMD allow (4096^2, 52 segments: 434 us at three
+    // waves, 401 at four).
+    template <int B, bool PC>
+    static constexpr auto walled_step()
+    {
+        if constexpr (B == 256 && PC && sizeof(typename PR::TU) == 4)
+            return &step_kernel_4<PR, B, PC, true>;
+        else
+            return &step_kernel<PR, B, PC, true>;
+    }
     template <int B, bool PC>
     static void step_w(const StepParams &sp, int nblocks, hipStream_t st)
     {
         if (sp.bc_lo != BC_PERIODIC)
-            hipLaunchKernelGGL((step_kernel<PR, B, PC, true>), dim3(nblocks), dim3(B), 0, st, sp);
+            hipLaunchKernelGGL((walled_step<B, PC>()), dim3(nblocks), dim3(B), 0, st, sp);
         else
             hipLaunchKernelGGL((step_kernel<PR, B, PC, false>), dim3(nblocks), dim3(B), 0, st, sp);
     }
@@ -208,8 +219,8 @@ struct Kernels {
             return 0;
         }
         if (pc)
-            return walled ? per_cu(step_kernel<PR, B, true, true>, B) : per_cu(step_kernel<PR, B, true, false>, B);
-        return walled ? per_cu(step_kernel<PR, B, false, true>, B) : per_cu(step_kernel<PR, B, false, false>, B);
+            return walled ? per_cu(walled_step<B, true>(), B) : per_cu(step_kernel<PR, B, true, false>, B);
+        return walled ? per_cu(walled_step<B, false>(), B) : per_cu(step_kernel<PR, B, false, false>, B);
     }
 
     // The entry points below are defined out of the class (not inline), so

@@ -1176,7 +1176,7 @@ __device__ __forceinline__ void step2_tile(const StepParams &p, const TileGeom &
 // L2. (Vertical neighbours reach their shared halo rows a whole segment
 // apart, long after L2 has dropped them.)
 template <class PR, int BLOCK, bool PC, bool WALLED>
-__global__ void __launch_bounds__(BLOCK) step_kernel(const StepParams p)
+__device__ __forceinline__ void step_block(const StepParams &p)
 {
     const int nb = p.n_strips * p.n_segs;
     const int bid = blockIdx.x;
@@ -1187,6 +1187,19 @@ __global__ void __launch_bounds__(BLOCK) step_kernel(const StepParams p)
     const int strip = logical - seg * p.n_strips;
     __shared__ TileLds<PR, BLOCK, PC, WALLED> lds;
     step_tile<PR, BLOCK, PC, WALLED>(p, tile_geom(p, strip, seg), lds);
+}
+
+template <class PR, int BLOCK, bool PC, bool WALLED>
+__global__ void __launch_bounds__(BLOCK) step_kernel(const StepParams p)
+{
+    step_block<PR, BLOCK, PC, WALLED>(p);
+}
+
+// The same held to four waves per SIMD.
+template <class PR, int BLOCK, bool PC, bool WALLED>
+__global__ void __launch_bounds__(BLOCK, 4) step_kernel_4(const StepParams p)
+{
+    step_block<PR, BLOCK, PC, WALLED>(p);
 }
 
 // One step over a list of tiles: the parts of a plate with x walls or holes
