@@ -148,13 +148,25 @@ lbm_status lbm_set_boundary(lbm_solver *h, lbm_edge e, lbm_bc bc, const double v
  * Synchronises the stream. Needs the material to be set first. */
 lbm_status lbm_set_fields(lbm_solver *h, const double *u0, const double *v0);
 
-/* Enqueue nsteps time steps on the stream and return at once. On a plate of
- * ten million sites or more with x walls or holes, each step (with the
- * predictor-corrector and 32- or 64-bit populations, each pair of steps)
- * runs the part clear of every wall and hole on the handle's stream and the
- * rest on a stream the library creates (default priority), forked and joined
- * with events: work enqueued on the handle's stream after lbm_step still
- * sees the whole step. */
+/* Enqueue nsteps time steps on the stream and return at once (the first call
+ * after a mask is set plans the plate on the host and waits for the upload of
+ * the plan). On a plate of ten million sites or more with x walls or holes
+ * (with holes, FP64 and the explicit scheme also 4.4 to 7 million), each step
+ * (with the predictor-corrector and 32- or 64-bit populations, each pair of
+ * steps) runs the part clear of every wall and hole on the handle's stream and
+ * the rest on a stream the library creates (default priority), forked and
+ * joined with events: work enqueued on the handle's stream after lbm_step
+ * still sees the whole step.
+ * May be captured into a graph. A graph of an even number of steps reads the
+ * copy of the state that it leaves it in, and so do eager calls of even
+ * numbers of steps from the first captured call of the handle on, and
+ * lbm_set_fields starts there: such graphs can be replayed with even eager
+ * calls and restarts between the replays. (An odd eager call moves the state
+ * to the other copy until the next odd one. Step counts, moving
+ * walls, the seed of stochastic rounding and the scale of 16-bit populations
+ * are those of the capture: a restart of a 16-bit plate needs a new one.) A
+ * captured call uploads no plan: a plate with a mask that has not stepped
+ * before runs as windows whole, slower on large plates. */
 lbm_status lbm_step(lbm_solver *h, int64_t nsteps);
 
 /* Read u, v = j / rho0, the first Piola-Kirchhoff stress P(H(u)) and the
@@ -235,12 +247,14 @@ lbm_status lbm_resident_blocks(const lbm_solver *h, int block, int steps_per_lau
 
 /* Run every step as the general step (1: 2D windows of the plate, each
  * holding its whole neighbourhood in registers and LDS) or, when no x edge is
- * a wall, as the fused step kernel (0). Both give the same results, bit for
- * bit where the fused kernel can run. The general step runs walls on the x
+ * a wall, as the fused step kernel (0). Both give the same results: bit for
+ * bit on periodic plates, up to rounding between y walls (where the library's
+ * own windows take the fused kernel's expressions). The general step runs walls on the x
  * edges, holes and the extrapolation scheme; on small plates it is also the
  * faster one (its stages run on the whole window in parallel where the fused
  * kernel marches rows one after another), and until this call or a launch
- * shape of the fused kernel is set the library picks it for them. Needs no
+ * shape of the fused kernel is set, or after lbm_set_default_plan, the library
+ * picks it for them. Needs no
  * workspace beyond what the plate's edges, mask and scheme already need. */
 lbm_status lbm_set_general_path(lbm_solver *h, int on);
 

@@ -26,7 +26,7 @@
 // stages (about 400 vector instructions a site on periodic plates, walls three
 // times that); on larger ones the issue of those instructions, with the rings
 // computed twice. Per step against the fused kernel's plan, which marches 12
-// or more dependent rows: 64^2 FP64 4.2 us (12.3), 256^2 FP32_U64 5.1 (16.4),
+// or more dependent rows: 64^2 FP64 4.4 us (12.3), 256^2 FP32_U64 5.1 (16.4),
 // 512^2 FP32_U64 9.5 (19.5), between y walls 10.9 (23.6); 100 x 150 with a hole
 // FP64 8.3 (29.1 with the 2D tiles these replace, which spent 1500 of 2500
 // vector instructions on index arithmetic, beside a fused share).
@@ -700,8 +700,8 @@ constexpr int kNumWinShapes = (int)(sizeof(kWinShapes) / sizeof(kWinShapes[0]));
 // windows, per class (double; float; float with a double displacement; 16-bit
 // storage) and kind of edges (WIN_*). A two-step
 // launch pays where the plate is small enough that the launch itself and the
-// load of the state count (64 x 64 FP64: 4.2 us per step with two 32 x 32
-// steps, 4.3 with 16 x 16 and 7.0 with 32 x 32 windows of one step).
+// load of the state count (64 x 64 FP64: 4.4 us per step with 32 x 32 windows of
+// two steps, 4.7 with 16 x 16 and 7.7 with 32 x 32 windows of one).
 struct WinCost {
     int shape, steps;
     float lat, lat1, base, thr;
